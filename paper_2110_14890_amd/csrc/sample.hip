@@ -48,12 +48,10 @@ namespace smore {
 namespace {
 
 constexpr int STAGE = 1024;   // LDS entries per wavefront for staged forward lists
-constexpr int LANE_SEG = 8;   // backward lists up to this length stay on one lane
 
-// Draw states.  ST_DEEP exists only inside the candidate kernel: the
-// candidate's backward list is short and it is tested after the shallow
-// pass over all survivors of the window.
-enum : int32_t { ST_NON = 0, ST_ANS = 1, ST_DUP = 2, ST_PEND = 3, ST_DEEP = 4 };
+// Draw states.  ST_DEEP exists only inside the candidate kernels: the
+// candidate has a backward list, which the deep pass tests.
+enum : int32_t { ST_NON = 0, ST_ANS = 1, ST_PEND = 3, ST_DEEP = 4 };
 
 // Accounting of graph reads (bytes, and the 64-byte lines they span).  The
 // verification kernel is instantiated with Tally when the caller asks for
@@ -77,33 +75,35 @@ struct Tally {
 };
 
 // Edges [x, y) of v under r when v's node-pointer pair (n0, n1) is known.
-template <class T>
-__device__ __forceinline__ int2 group_from(const DirView& d, int32_t n0, int32_t n1, int32_t r, T& tl)
-{
-    int32_t lo = n0, hi = n1;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        tl.read(&d.grp[mid].x, 4);
-        if (d.grp[mid].x < r) lo = mid + 1; else hi = mid;
-    }
-    if (lo < n1 && d.grp[lo].x == r) {
-        tl.read(&d.grp[lo].y, 4);
-        tl.read(&d.grp[lo + 1].y, 4);
-        return make_int2(d.grp[lo].y, d.grp[lo + 1].y);
-    }
-    return make_int2(0, 0);
-}
-
-// group_from for an entity with at most SCAN groups: all of its group
-// entries (and the next one, for the end bound) are loaded at once, so the
-// lookup is one dependent step instead of a chain of binary-search probes.
+// The entries of the last SCAN groups in question (and the next one, for the
+// end bound) are loaded at once, so the lookup of an entity with no more
+// than that is one dependent step.
 constexpr int SCAN = 8;
+
+// One step of an eight-way search of the n > SCAN groups from lo for
+// relation r: seven probes at once, after which the group, if the entity
+// has it, is among the n left.
+template <class T>
+__device__ __forceinline__ void group_narrow(const DirView& d, int32_t& lo, int32_t& n, int32_t r, T& tl)
+{
+    const int32_t q = n >> 3;
+    int32_t v[7], c = 0;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        v[k] = d.grp[lo + q * (k + 1)].x;
+        tl.read(&d.grp[lo + q * (k + 1)].x, 4);
+    }
+#pragma unroll
+    for (int k = 0; k < 7; ++k) c += v[k] <= r;
+    lo += q * c;
+    n = c == 7 ? n - 7 * q : q;
+}
 
 template <class T>
 __device__ __forceinline__ int2 group_find(const DirView& d, int32_t n0, int32_t n1, int32_t r, T& tl)
 {
-    const int32_t n = n1 - n0;
-    if (n > SCAN) return group_from(d, n0, n1, r, tl);
+    int32_t n = n1 - n0;
+    while (n > SCAN) group_narrow(d, n0, n, r, tl);
     if (n <= 0) return make_int2(0, 0);
     int2 e[SCAN + 1];
 #pragma unroll
@@ -116,32 +116,40 @@ __device__ __forceinline__ int2 group_find(const DirView& d, int32_t n0, int32_t
     return res;
 }
 
-// group_find of two entities at once (the loads of both scans in flight
-// together); inactive entries return (0, 0).
+// group_find of two entities at once (the loads of both in flight together);
+// inactive entries return (0, 0).  Entities with more than SCAN groups are
+// narrowed eight ways per step first: a wavefront waits for its widest
+// lane, and one of 535 groups is three dependent reads and the scan in place
+// of ten.
 template <class T>
 __device__ __forceinline__ void group_find2(const DirView& d, const int32_t* n0, const int32_t* n1,
                                             const bool* act, int32_t r, int2* res, T& tl)
 {
+    int32_t lo[2], n[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        lo[u] = n0[u];
+        n[u] = act[u] ? n1[u] - n0[u] : 0;
+    }
+    while (n[0] > SCAN || n[1] > SCAN) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (n[u] > SCAN) group_narrow(d, lo[u], n[u], r, tl);
+    }
     int2 e[2][SCAN + 1];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int32_t n = act[u] ? n1[u] - n0[u] : 0;
 #pragma unroll
         for (int k = 0; k <= SCAN; ++k)
-            e[u][k] = (n > 0 && n <= SCAN && k <= n) ? d.grp[n0[u] + k] : make_int2(INT_MAX, 0);
-        if (n > 0 && n <= SCAN) tl.read(d.grp + n0[u], 8 * (n + 1));
+            e[u][k] = (n[u] > 0 && k <= n[u]) ? d.grp[lo[u] + k] : make_int2(INT_MAX, 0);
+        if (n[u] > 0) tl.read(d.grp + lo[u], 8 * (n[u] + 1));
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int32_t n = act[u] ? n1[u] - n0[u] : 0;
         res[u] = make_int2(0, 0);
-        if (n > SCAN) {
-            res[u] = group_from(d, n0[u], n1[u], r, tl);
-        } else {
 #pragma unroll
-            for (int k = 0; k < SCAN; ++k)
-                if (k < n && e[u][k].x == r) res[u] = make_int2(e[u][k].y, e[u][k + 1].y);
-        }
+        for (int k = 0; k < SCAN; ++k)
+            if (k < n[u] && e[u][k].x == r) res[u] = make_int2(e[u][k].y, e[u][k + 1].y);
     }
 }
 
@@ -161,11 +169,10 @@ __device__ __forceinline__ int2 group_range(const DirView& d, int32_t v, int32_t
     return group_range(d, v, r, t);
 }
 
-// A sorted entity list, staged in LDS (lds = true) or read in place.
+// A sorted entity list in memory.
 struct FSet {
     const int32_t* p;
     int32_t n;
-    bool lds;
 };
 
 template <class T>
@@ -181,26 +188,12 @@ __device__ __forceinline__ bool has(const int32_t* p, int32_t n, int32_t x, bool
     return lo < n && p[lo] == x;
 }
 
-// Membership in a forward-cached list.  The list itself is accounted once
-// per query when it is cached; lookups in it are not graph traffic of the
-// method, wherever the list lives.
-template <class T>
-__device__ __forceinline__ bool has(const FSet& s, int32_t x, T&)
-{
-    NoTally none;
-    return has(s.p, s.n, x, false, none);
-}
-
 // Wave-uniform copy of a value every lane holds (the compiler then keeps
 // loops and exits that depend on it converged).
 __device__ __forceinline__ int32_t uni(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // Lane k's copy of a value (k wave-uniform).
 __device__ __forceinline__ int32_t readlane(int32_t x, int k) { return __builtin_amdgcn_readlane(x, k); }
-__device__ __forceinline__ int64_t readlane64(int64_t x, int k)
-{
-    return (int64_t)(uint32_t)readlane((int32_t)x, k) | ((int64_t)readlane((int32_t)(x >> 32), k) << 32);
-}
 
 __device__ __forceinline__ uint64_t lanes_below(int lane)
 {
@@ -602,6 +595,10 @@ SHAPE(QPNI, 2, 2, 3, 0, 1, 0, 0, 2, 0, 1, 0, 0)
 // is a forward-cached set the deep test needs staged.
 template <int QT> constexpr bool chain_r1 = QT == Q2P || QT == QPI || QT == QPIN || QT == QPNI;
 template <int QT> constexpr bool two_cached = QT == QIP || QT == QUP || QT == QINP;
+// Shapes with a backward step that can meet a long list (the others decide
+// every candidate by edge tests).
+template <int QT> constexpr bool has_long_lists = QT == Q2P || QT == Q3P || QT == QPI || QT == QPIN ||
+                                                  QT == QPNI || two_cached<QT>;
 
 // Lists that test a candidate by one edge into the root: c is an answer
 // only if c is in list f for every f of `mask` (any f when `any`).  When
@@ -645,6 +642,7 @@ constexpr int CWG = 64;
 constexpr int HEAVY_WG = 256;    // threads of the heavy-queue workgroups
 constexpr int QF = 8;            // int32 per query in the per-query block
 constexpr int PERSIST_BLOCKS = 2048;
+constexpr int FINISH_BLOCKS = 4096;   // one-wave workgroups of the finishing kernel
 // 3p long-list work in bounded units: the long-list kernel expands at most
 // UNIT_Y entities y of an item and searches at most UNIT_PAIRS pairs of one
 // y itself; the rest become units of the unit queue (UNITS_PER_QUERY slots
@@ -693,36 +691,37 @@ __device__ __forceinline__ int32_t candidate(const SampleParams& p, int32_t V, i
 // takes every query still short to neg_tries.  Rounds are a scheduling
 // detail: a query's negatives are its first n_neg accepted draws in draw
 // order whatever the rounds were.
-inline int32_t first_round(const SampleParams& p)
+inline int32_t first_margin(const SampleParams& p)
 {
     const int64_t e = (int64_t)p.n_neg + p.n_neg / 32 + 8;
     return (int32_t)(e < p.neg_tries ? e : p.neg_tries);
 }
 
-// Three rounds (first, own ranges, the rest); a batch under 4,096 queries
-// is bound by launches rather than draws, and its second round takes the
-// rest of the budget at once.
-inline int n_rounds(const SampleParams& p)
-{
-    if (first_round(p) >= p.neg_tries) return 1;
-    return p.batch >= 4096 ? 3 : 2;
-}
-
-// Longest range one query takes in one round.
+// Entries per query of the long-list queue.
 inline int32_t max_round_len(const SampleParams& p)
 {
-    const int32_t e0 = first_round(p);
+    const int32_t e0 = first_margin(p);
     return e0 > p.neg_tries - e0 ? e0 : p.neg_tries - e0;
+}
+
+// A batch under 4,096 queries does not fill the GPU's wavefronts, and its
+// time is that of its slowest ones: there the first round fills its last 64
+// draws up (they cost no further step), so that fewer queries need another
+// chain of dependent reads.  Above, the draws themselves are the cost.  The
+// queue has to hold the round.
+inline int32_t first_round(const SampleParams& p)
+{
+    const int32_t e = first_margin(p);
+    if (p.batch >= 4096) return e;
+    return max(e, min((e + 16 + 63) / 64 * 64, min(p.neg_tries, max_round_len(p))));
 }
 
 // End of the next range of a query that has `kept` accepted draws among its
 // first `end`: the deficit over that acceptance rate, a quarter more, and
-// 16 draws; everything up to neg_tries when nothing was accepted yet or the
-// next round is the last.
-__device__ __forceinline__ int32_t next_round_end(const SampleParams& p, int32_t end, int32_t kept,
-                                                  bool to_last)
+// 16 draws; everything up to neg_tries when nothing was accepted yet.
+__device__ __forceinline__ int32_t next_round_end(const SampleParams& p, int32_t end, int32_t kept)
 {
-    if (to_last || kept <= 0) return p.neg_tries;
+    if (kept <= 0) return p.neg_tries;
     const int64_t need = (int64_t)(p.n_neg - kept) * end;
     const int64_t more = (need * 5 + 4 * (int64_t)kept - 1) / (4 * (int64_t)kept) + 16;
     return (int32_t)(end + more < p.neg_tries ? end + more : p.neg_tries);
@@ -777,62 +776,135 @@ __device__ __forceinline__ void flush_tally(T& tl, int64_t* stats, int32_t b, in
     }
 }
 
-// Is (a, r, c) an edge?  From the anchor's list when it is staged in LDS,
-// otherwise from c's reverse list under r (c's node pair already loaded).
+// LDS of one wavefront of the candidate kernels.  Staged lists keep their
+// order in `stage` and have a hashed bit set each in `bits` (split evenly
+// between the shape's lists): a value whose bit is clear is not in the list,
+// so one LDS read settles nearly every lookup, and only the others bisect
+// the list.  The sizes keep it at 10,240 bytes, eight of the 1,280-byte units
+// that LDS is given out in: 16 wavefronts per CU, as their registers allow.
+constexpr int WIN = 576;
+constexpr int DPW = WIN / 64;
+constexpr int WORDS = WIN / 32;
+constexpr int DEEPQ = 192;       // deep items held before a pass over 64 of them: 63 + one step of 128
+constexpr int BIT_WORDS = 256;
+struct alignas(16) WaveLds {
+    int32_t stage[STAGE];
+    uint32_t bits[BIT_WORDS];
+    int32_t cand[WIN];      // the window's candidates (complemented: left to the long-list kernels)
+    int32_t ds[DEEPQ];      // deep items: start of the backward list
+    uint16_t dl[DEEPQ];     //             its length, at most 65,535
+    uint16_t dj[DEEPQ];     //             index in the window
+    uint16_t sj[WIN];       // survivors of the first test: index in the window
+    uint32_t non[WORDS];    // bit i: candidate i is a non-answer
+};
+
+static_assert(sizeof(WaveLds) <= 10240, "LDS of a wavefront");
+
+// A query's forward-cached list: edges [beg, beg + n), and where it is staged.
+struct FList {
+    int32_t beg, n, off;
+    bool lds;
+};
+
+// log2 of the bits per list
+template <int QT> constexpr int bit_log = Shape<QT>::nf == 1 ? 13 : Shape<QT>::nf == 2 ? 12 : 11;
+template <int QT> __device__ __forceinline__ uint32_t bit_slot(int f, int32_t x)
+{
+    return ((uint32_t)f << bit_log<QT>) | (((uint32_t)x * 0x9E3779B1u) >> (32 - bit_log<QT>));
+}
+template <int QT> __device__ __forceinline__ bool maybe_in(const WaveLds& L, int f, int32_t x)
+{
+    const uint32_t h = bit_slot<QT>(f, x);
+    return L.bits[h >> 5] >> (h & 31) & 1u;
+}
+
+// Is x in the staged list F?
+__device__ __forceinline__ bool in_stage(const WaveLds& L, const FList& F, int32_t x)
+{
+    int32_t lo = F.off, hi = F.off + F.n;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (L.stage[mid] < x) lo = mid + 1; else hi = mid;
+    }
+    return lo < F.off + F.n && L.stage[lo] == x;
+}
+
+// Is x in the sorted list p[0..n)?  Seven probes per step where eight or
+// more entries remain: a third of the dependent reads of a bisection.
 template <class T>
-__device__ __forceinline__ bool edge_test(const GraphView& g, const FSet& Fa, int32_t a, int32_t r,
-                                          int32_t c, int32_t n0, int32_t n1, T& tl)
+__device__ __forceinline__ bool has8(const int32_t* p, int32_t n, int32_t x, bool count, T& tl)
 {
-    if (Fa.lds) return has(Fa, c, tl);
+    while (n >= 8) {
+        const int32_t q = n >> 3;
+        int32_t v[7], c = 0;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            v[k] = p[q * (k + 1)];
+            if (count) tl.read(p + q * (k + 1), 4);
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k) c += v[k] <= x;
+        p += q * c;
+        n = c == 7 ? n - 7 * q : q;
+    }
+    bool hit = false;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        if (k < n) {
+            if (count) tl.read(p + k, 4);
+            hit = hit || p[k] == x;
+        }
+    }
+    return hit;
+}
+
+// Membership in list f.  The list is accounted once per query when it is
+// cached; lookups in it are not graph traffic of the method, wherever the
+// list lives.
+template <int QT>
+__device__ __forceinline__ bool in_list(const GraphView& g, const WaveLds& L, const FList* F, int f,
+                                        int32_t x)
+{
+    NoTally none;
+    if (F[f].lds) return maybe_in<QT>(L, f, x) && in_stage(L, F[f], x);
+    return has8(g.fwd.nbr + F[f].beg, F[f].n, x, false, none);
+}
+
+// Is (a, r, c) an edge?  From the anchor's list (f) when it is staged,
+// otherwise from c's reverse list under r (c's node pair already loaded).
+template <int QT, class T>
+__device__ __forceinline__ bool edge_test(const GraphView& g, const WaveLds& L, const FList* F, int f,
+                                          int32_t a, int32_t r, int32_t c, int32_t n0, int32_t n1, T& tl)
+{
+    if (F[f].lds) return maybe_in<QT>(L, f, c) && in_stage(L, F[f], c);
     const int2 s = group_find(g.rev, n0, n1, r, tl);
-    return s.y > s.x && has(g.rev.nbr + s.x, s.y - s.x, a, true, tl);
+    return s.y > s.x && has8(g.rev.nbr + s.x, s.y - s.x, a, true, tl);
 }
 
-// First, shallow decision for candidate c at lane level: ST_NON or ST_ANS
-// when it is settled by the cached lists and c's own groups, ST_PEND when a
-// wavefront must intersect a long list, ST_DEEP with c's backward list
-// [lst.x, lst.y) when that list is short and is to be tested next.
+// Decision of a shape made of edge tests alone.
 template <int QT, class T>
-__device__ __forceinline__ int32_t shallow_test(const GraphView& g, const FSet* F, const int32_t* anc,
-                                                const int32_t* rel, int32_t c, int32_t n0, int32_t n1,
-                                                int2& lst, T& tl)
+__device__ __forceinline__ int32_t edges_decide(const GraphView& g, const WaveLds& L, const FList* F,
+                                                const int32_t* anc, const int32_t* rel, int32_t c,
+                                                int32_t n0, int32_t n1, T& tl)
 {
-    if (QT == Q1P) return edge_test(g, F[0], anc[0], rel[0], c, n0, n1, tl) ? ST_ANS : ST_NON;
-    if (QT == Q2I)
-        return (edge_test(g, F[0], anc[0], rel[0], c, n0, n1, tl) &&
-                edge_test(g, F[1], anc[1], rel[1], c, n0, n1, tl)) ? ST_ANS : ST_NON;
-    if (QT == Q3I)
-        return (edge_test(g, F[0], anc[0], rel[0], c, n0, n1, tl) &&
-                edge_test(g, F[1], anc[1], rel[1], c, n0, n1, tl) &&
-                edge_test(g, F[2], anc[2], rel[2], c, n0, n1, tl)) ? ST_ANS : ST_NON;
-    if (QT == Q2U)
-        return (edge_test(g, F[0], anc[0], rel[0], c, n0, n1, tl) ||
-                edge_test(g, F[1], anc[1], rel[1], c, n0, n1, tl)) ? ST_ANS : ST_NON;
-    if (QT == Q2IN)
-        return (edge_test(g, F[0], anc[0], rel[0], c, n0, n1, tl) &&
-                !edge_test(g, F[1], anc[1], rel[1], c, n0, n1, tl)) ? ST_ANS : ST_NON;
-    if (QT == Q3IN)
-        return (edge_test(g, F[0], anc[0], rel[0], c, n0, n1, tl) &&
-                edge_test(g, F[1], anc[1], rel[1], c, n0, n1, tl) &&
-                !edge_test(g, F[2], anc[2], rel[2], c, n0, n1, tl)) ? ST_ANS : ST_NON;
-    if ((QT == QPI || QT == QPNI) && !edge_test(g, F[1], anc[1], rel[2], c, n0, n1, tl)) return ST_NON;
-    if (QT == QPIN && edge_test(g, F[1], anc[1], rel[2], c, n0, n1, tl)) return ST_NON;
-    // backward step from c under the relation entering the root; for pni a
-    // meeting chain puts c in the complemented set
-    const int32_t rb = chain_r1<QT> ? rel[1] : rel[2];
-    const int2 s = group_find(g.rev, n0, n1, rb, tl);
-    if (s.y == s.x) return QT == QPNI ? ST_ANS : ST_NON;
-    if (s.y - s.x > LANE_SEG || !F[0].lds || (two_cached<QT> && !F[1].lds)) return ST_PEND;
-    lst = s;
-    return ST_DEEP;
+    auto edge = [&](int f) { return edge_test<QT>(g, L, F, f, anc[f], rel[f], c, n0, n1, tl); };
+    bool ans = edge(0);
+    if (QT == Q2I || QT == Q3I || QT == Q3IN) ans = ans && edge(1);
+    if (QT == Q2U) ans = ans || edge(1);
+    if (QT == Q2IN) ans = ans && !edge(1);
+    if (QT == Q3I) ans = ans && edge(2);
+    if (QT == Q3IN) ans = ans && !edge(2);
+    return ans ? ST_ANS : ST_NON;
 }
 
-// shallow_test of two candidates c[0], c[1] (act[u]: slot in use) with the
-// dependent steps of both interleaved.
+// First, shallow decision of two candidates c[0], c[1] (act[u]: slot in use)
+// at lane level, with the dependent steps of both interleaved: ST_NON or
+// ST_ANS when it is settled by the cached lists and c's own groups, else
+// ST_DEEP with c's backward list [lst.x, lst.y).
 template <int QT, class T>
-__device__ __forceinline__ void shallow_test2(const GraphView& g, const FSet* F, const int32_t* anc,
-                                              const int32_t* rel, const int32_t* c, const bool* act,
-                                              int32_t* st, int2* lst, T& tl)
+__device__ __forceinline__ void shallow_test2(const GraphView& g, const WaveLds& L, const FList* F,
+                                              const int32_t* anc, const int32_t* rel, const int32_t* c,
+                                              const bool* act, int32_t* st, int2* lst, T& tl)
 {
     int32_t n0[2], n1[2];
 #pragma unroll
@@ -844,10 +916,10 @@ __device__ __forceinline__ void shallow_test2(const GraphView& g, const FSet* F,
             tl.read(g.rev.node + c[u], 8);
         }
     }
-    if (QT == Q1P || QT == Q2I || QT == Q3I || QT == Q2U || QT == Q2IN || QT == Q3IN) {
+    if constexpr (!has_long_lists<QT>) {
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-            st[u] = act[u] ? shallow_test<QT>(g, F, anc, rel, c[u], n0[u], n1[u], lst[u], tl) : ST_NON;
+            st[u] = act[u] ? edges_decide<QT>(g, L, F, anc, rel, c[u], n0[u], n1[u], tl) : ST_NON;
         return;
     }
     bool live[2];
@@ -855,7 +927,7 @@ __device__ __forceinline__ void shallow_test2(const GraphView& g, const FSet* F,
     for (int u = 0; u < 2; ++u) {
         live[u] = act[u];
         if (QT == QPI || QT == QPNI || QT == QPIN) {
-            const bool e = act[u] && edge_test(g, F[1], anc[1], rel[2], c[u], n0[u], n1[u], tl);
+            const bool e = act[u] && edge_test<QT>(g, L, F, 1, anc[1], rel[2], c[u], n0[u], n1[u], tl);
             live[u] = act[u] && (QT == QPIN ? !e : e);
         }
     }
@@ -868,10 +940,6 @@ __device__ __forceinline__ void shallow_test2(const GraphView& g, const FSet* F,
         if (!live[u]) continue;
         if (sr[u].y == sr[u].x) {
             if (QT == QPNI) st[u] = ST_ANS;   // nothing reaches c through the complemented chain
-            continue;
-        }
-        if (sr[u].y - sr[u].x > LANE_SEG || !F[0].lds || (two_cached<QT> && !F[1].lds)) {
-            st[u] = ST_PEND;
         } else {
             lst[u] = sr[u];
             st[u] = ST_DEEP;
@@ -879,65 +947,146 @@ __device__ __forceinline__ void shallow_test2(const GraphView& g, const FSet* F,
     }
 }
 
-// Then the deep decision: the backward list y[0..len) of c (len <= LANE_SEG)
-// against the staged forward list(s); for 3p one more backward step from
-// every y.
-template <int QT, class T>
-__device__ __forceinline__ int32_t deep_test(const GraphView& g, const FSet* F, const int32_t* rel,
-                                             int32_t start, int32_t len, T& tl)
+// Highest lane whose exclusive prefix excl is <= idx (binary lifting over
+// the wavefront; every lane must be active).  excl is nondecreasing over
+// the lanes and 0 in lane 0.
+__device__ __forceinline__ int owner_lane(int32_t idx, int32_t excl)
 {
-    int32_t y[LANE_SEG];
+    int lo = 0;
 #pragma unroll
-    for (int k = 0; k < LANE_SEG; ++k) y[k] = k < len ? g.rev.nbr[start + k] : -1;
-    tl.read(g.rev.nbr + start, 4 * len);
-    if (QT != Q3P) {
-        bool hit = false;
-#pragma unroll
-        for (int k = 0; k < LANE_SEG; ++k) {
-            if (k >= len) break;
-            if (chain_r1<QT>) hit = hit || has(F[0], y[k], tl);
-            else if (QT == QIP) hit = hit || (has(F[0], y[k], tl) && has(F[1], y[k], tl));
-            else if (QT == QINP) hit = hit || (has(F[0], y[k], tl) && !has(F[1], y[k], tl));
-            else hit = hit || has(F[0], y[k], tl) || has(F[1], y[k], tl);
-        }
-        // pni: a meeting chain means c is in the complemented set
-        return (QT == QPNI ? !hit : hit) ? ST_ANS : ST_NON;
+    for (int step = 32; step >= 1; step >>= 1) {
+        const int cand = lo + step;
+        const int32_t ev = __shfl(excl, cand > 63 ? 63 : cand);
+        if (cand <= 63 && ev <= idx) lo = cand;
     }
-    // 3p: node pairs and signatures of every y at once, then each y's
-    // group under r1 (skipped when y's signature lacks r1's class: y then
-    // has no in-edge under r1)
-    int32_t a0[LANE_SEG], a1[LANE_SEG];
-    uint32_t sg[LANE_SEG];
+    return lo;
+}
+
+__device__ __forceinline__ int32_t excl_prefix(int32_t v, int lane, int32_t* total)
+{
+    int32_t incl = v;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+    }
+    *total = uni(__shfl(incl, 63));
+    return incl - v;
+}
+
+// The deep pass over up to 64 candidates, one per lane: lane l's candidate
+// has the backward list [start, start + len) (len 0: none).  Returns the
+// lanes whose chain meets the cached lists, and in *pend those left to a
+// whole wavefront.  The entries y of all lists are laid out over the lanes,
+// 64 per step; for 3p so are the (y, key) pairs of each 64 y's, keys from the
+// shorter of R_r1(y) and F0.  So the dependent reads of the pass are those
+// of its deepest candidate, not the sum over a lane's entries (one lane
+// walking its own list: 172 + 77 us in two rounds for 512 3p queries x 128
+// on an FB15k-237-shaped graph; laid out: 67 us for all draws).  A list over DEEP_LONG
+// entries, or past DEEP_TOTAL entries of the pass, is left, and so is
+// everything once the query has taken DEEP_STEPS steps (`steps` counts them
+// down): a wavefront of its own (or, for 3p, several) shortens the longest
+// wavefront of the call.
+constexpr int DEEP_LONG = 512, DEEP_TOTAL = 4096, DEEP_STEPS = 48;
+
+// Drops from len the lists the pass leaves; returns the lanes dropped.
+__device__ __forceinline__ uint64_t deep_limit(int32_t& len, int lane)
+{
+    bool over = len > DEEP_LONG;
+    if (over) len = 0;
+    int32_t tot;
+    const int32_t ex = excl_prefix(len, lane, &tot);
+    if (tot > DEEP_TOTAL) {
+        over = over || (len > 0 && ex + len > DEEP_TOTAL);
+        if (over) len = 0;
+    }
+    return __ballot(over);
+}
+
+// Bits of the owners of the lanes where `hit` holds.
+__device__ __forceinline__ uint64_t owners_of(bool hit, int owner)
+{
+    uint64_t m = __ballot(hit), res = 0;
+    while (m) {
+        res |= 1ull << readlane(owner, __ffsll((unsigned long long)m) - 1);
+        m &= m - 1;
+    }
+    return res;
+}
+
+template <int QT, class T>
+__device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds& L, const FList* F,
+                                              const int32_t* rel, int32_t start, int32_t len, int lane,
+                                              int32_t& steps, uint64_t* pend, T& tl)
+{
+    uint64_t left = deep_limit(len, lane), ans = 0;
+    int32_t total;
+    const int32_t ex = excl_prefix(len, lane, &total);
     const uint32_t b1 = sig_bit(rel[1]);
-#pragma unroll
-    for (int k = 0; k < LANE_SEG; ++k) {
-        a0[k] = 0;
-        a1[k] = 0;
-        sg[k] = 0;
-        if (k < len) {
-            a0[k] = g.rev.node[y[k]];
-            a1[k] = g.rev.node[y[k] + 1];
-            sg[k] = g.sig[y[k]];
-            tl.read(g.rev.node + y[k], 8);
-            tl.read(g.sig + y[k], 1);
+    for (int32_t y0 = 0; y0 < total; y0 += 64) {
+        if (--steps < 0) {   // the lists that reach past entry y0
+            left |= __ballot(len > 0 && ex + len > y0);
+            break;
+        }
+        const bool on = y0 + lane < total;
+        const int it = owner_lane(min(y0 + lane, total - 1), ex);
+        const int32_t at = __shfl(start, it) + y0 + lane - __shfl(ex, it);
+        int32_t y = -1;
+        if (on) {
+            y = g.rev.nbr[at];
+            tl.read(g.rev.nbr + at, 4);
+        }
+        if constexpr (QT != Q3P) {
+            bool hit = false;
+            if (on) {
+                hit = in_list<QT>(g, L, F, 0, y);
+                if (QT == QIP) hit = hit && in_list<QT>(g, L, F, 1, y);
+                if (QT == QINP) hit = hit && !in_list<QT>(g, L, F, 1, y);
+                if (QT == QUP) hit = hit || in_list<QT>(g, L, F, 1, y);
+            }
+            ans |= owners_of(hit, it);
+        } else {
+            // y without an in-edge under r1's signature class has none under r1
+            int2 s2 = make_int2(0, 0);
+            if (on && !((ans | left) >> it & 1)) {
+                tl.read(g.sig + y, 1);
+                const int32_t a0 = g.rev.node[y], a1 = g.rev.node[y + 1];
+                if (g.sig[y] & b1) {
+                    tl.read(g.rev.node + y, 8);
+                    s2 = group_find(g.rev, a0, a1, rel[1], tl);
+                }
+            }
+            const int32_t n2 = s2.y - s2.x, nf = F[0].n;
+            int32_t np = min(n2, nf);
+            left |= owners_of(np > DEEP_LONG, it);
+            const uint64_t over = deep_limit(np, lane);
+            if (over) left |= owners_of(over >> lane & 1, it);
+            int32_t ptotal;
+            const int32_t pex = excl_prefix(np, lane, &ptotal);
+            for (int32_t p0 = 0; p0 < ptotal; p0 += 64) {
+                if (--steps < 0) {
+                    left |= owners_of(np > 0 && pex + np > p0, it);
+                    break;
+                }
+                const int yl = owner_lane(min(p0 + lane, ptotal - 1), pex);
+                const int32_t off = p0 + lane - __shfl(pex, yl);
+                const int32_t lx = __shfl(s2.x, yl), ln = __shfl(n2, yl);
+                const int who = __shfl(it, yl);
+                bool hit = false;
+                if (p0 + lane < ptotal && !((ans | left) >> who & 1)) {
+                    if (ln <= nf) {
+                        tl.read(g.rev.nbr + lx + off, 4);
+                        hit = in_list<QT>(g, L, F, 0, g.rev.nbr[lx + off]);
+                    } else {
+                        const int32_t x = F[0].lds ? L.stage[F[0].off + off] : g.fwd.nbr[F[0].beg + off];
+                        hit = has8(g.rev.nbr + lx, ln, x, true, tl);
+                    }
+                }
+                ans |= owners_of(hit, who);
+            }
         }
     }
-    for (int k = 0; k < len; ++k) {
-        if (!(sg[k] & b1)) continue;
-        const int2 s2 = group_find(g.rev, a0[k], a1[k], rel[1], tl);
-        const int32_t n2 = s2.y - s2.x;
-        if (n2 > LANE_SEG) return ST_PEND;
-        int32_t x[LANE_SEG];
-#pragma unroll
-        for (int m = 0; m < LANE_SEG; ++m) x[m] = m < n2 ? g.rev.nbr[s2.x + m] : -1;
-        tl.read(g.rev.nbr + s2.x, 4 * n2);
-        bool hit = false;
-#pragma unroll
-        for (int m = 0; m < LANE_SEG; ++m)
-            if (m < n2) hit = hit || has(F[0], x[m], tl);
-        if (hit) return ST_ANS;
-    }
-    return ST_NON;
+    *pend = left & ~ans;
+    return ans;
 }
 
 // Wavefront decision for a queued candidate (the one-hop operand of
@@ -1053,20 +1202,15 @@ __global__ __launch_bounds__(256) void k_prepare(GraphView g, SampleParams p, sm
     const int32_t b = gid >> 2;
     const int f = gid & 3;
     if (b >= p.batch) return;   // whole groups: 4 divides the workgroup size
-    if (gid == 0) {   // queue and list counters of the first round: every query is listed
+    if (gid == 0) {   // counters: queued pairs, queries to finish, units
         ws.ctrl[0] = 0;
-        ws.ctrl[1] = 0;
-        ws.ctrl[2] = p.batch;
-        ws.ctrl[3] = 0;
+        ws.ctrl[2] = 0;
         ws.ctrl[5] = 0;
     }
     int32_t anc[3], rel[3];
     int32_t* q = ws.qf + (int64_t)b * QF;
-    if (f == 0) {
-        ws.act[0][b] = b;
-        if (stats)
-            for (int k = 0; k < 4; ++k) stats[4 * (int64_t)b + k] = 0;
-    }
+    if (f == 0 && stats)
+        for (int k = 0; k < 4; ++k) stats[4 * (int64_t)b + k] = 0;
     if (!query_ok(g, out, b, Shape<QT>::n_anc, Shape<QT>::n_rel, R, anc, rel)) {
         if (f == 0) {
             write_undrawn_row(p, out, b, false);
@@ -1124,17 +1268,14 @@ __global__ __launch_bounds__(256) void k_no_draws(GraphView g, SampleParams p, s
         for (int k = 0; k < 4; ++k) stats[4 * (int64_t)b + k] = 0;
 }
 
-// One wavefront per active query, in one-wave workgroups: a workgroup per
-// query in the first round, persistent over the list in later rounds (no
-// workgroup barrier).  The query's lists are
-// staged once into the wave's LDS slice.  Draws are taken WIN at a time:
-// every lane computes WIN / 64 draws and reads their in-edge bits (all
-// loads in flight together); the draws with an in-edge are compacted into
-// the wave's survivor list and then verified one per lane, so a window
-// costs one dependent chain per 64 survivors instead of one per draw slot.
-constexpr int WIN = 576;
-constexpr int DPW = WIN / 64;
-static_assert(SMORE_MAX_NEG_TRIES <= 4096 && LANE_SEG <= 8, "deep items pack j and length in 15 bits");
+// The candidate kernels run one wavefront per query.  The query's lists are
+// staged once into the wave's LDS slice.  Draws are taken a window of at
+// most WIN at a time: every lane computes WIN / 64 draws and reads their
+// in-edge bits (all loads in flight together); the draws with an in-edge are
+// compacted into the wave's survivor list and then verified one per lane, so
+// a window costs one dependent chain per 64 survivors instead of one per
+// draw slot.  The window's candidates stay in LDS, its verdicts in one bit
+// per draw, and the same wavefront selects the window's negatives.
 
 __device__ __forceinline__ void wave_sync()
 {
@@ -1143,215 +1284,510 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// SH: the candidates are the minibatch's shared set p.shared (j < its
-// size) instead of the query's own draws.
-template <int QT, class T, bool SH = false>
-__global__ __launch_bounds__(CWG) void k_candidates(GraphView g, SampleParams p, smore_sample_out out,
-                                                    Ws ws, int64_t* stats, int cur, int32_t j0,
-                                                    int32_t j1)
+// First-occurrence table of the selection: tcap values in LDS, its own
+// (own = 1) or over the staged lists and their bits.  At most 13/16 of it is
+// filled: a window after the first holds that many draws less the values
+// kept before it.
+struct Table {
+    int32_t tcap, own;
+};
+constexpr int TABLE_OVER = STAGE + BIT_WORDS;
+__host__ __device__ __forceinline__ int32_t table_room(int32_t tcap) { return tcap / 16 * 13; }
+__device__ __forceinline__ uint32_t table_slot(int32_t tcap, int32_t c)
 {
-    if constexpr (SH)
-        if (p.n_shared) j1 = min(j1, uni(*p.n_shared));
-    __shared__ int32_t stage_all[CWG / 64][STAGE];
-    __shared__ int32_t sc_all[CWG / 64][WIN];
-    __shared__ uint16_t sj_all[CWG / 64][WIN];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t* stage = stage_all[w];
-    int32_t* sc = sc_all[w];
-    uint16_t* sj = sj_all[w];
+    return __umulhi((uint32_t)c * 0x9E3779B1u, (uint32_t)tcap);
+}
+__device__ __forceinline__ uint32_t table_next(int32_t tcap, uint32_t h)
+{
+    return h + 1 == (uint32_t)tcap ? 0 : h + 1;
+}
+
+// Table holding the first acc negatives of a row (all its kept values).
+__device__ __forceinline__ void table_fill(int32_t* tab, int32_t tcap, const int32_t* row, int32_t acc,
+                                           int lane)
+{
+    for (int32_t k = 4 * lane; k < tcap; k += 256) *(int4*)(tab + k) = make_int4(-1, -1, -1, -1);
+    if (acc > 0) {
+        // rows are written by this wave, or by an earlier kernel
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+    wave_sync();
+    for (int32_t k = lane; k < acc; k += 64) {
+        const int32_t c = row[k];
+        uint32_t h = table_slot(tcap, c);
+        while (atomicCAS(&tab[h], -1, c) != -1) h = table_next(tcap, h);
+    }
+    wave_sync();
+}
+
+// Ordered selection over one window: candidate i < n (draw j0 + i) is kept
+// iff it is a non-answer and no earlier draw had its value; the first n_neg
+// kept are the row.  Answers never enter the table: a value has the same
+// verdict at each of its draws.  A lane's first probes are in flight
+// together, and only the values that met another one probe on.  Returns the
+// row's length after the window.
+__device__ __forceinline__ int32_t select_window(const SampleParams& p, const smore_sample_out& out,
+                                                 int32_t b, WaveLds& L, int32_t* tab, int32_t tcap,
+                                                 int32_t j0, int32_t n, int32_t acc, int lane)
+{
     const uint64_t below = lanes_below(lane);
-    const int32_t nact = uni(ws.ctrl[2 + cur]);
-    const int32_t nwaves = gridDim.x * (CWG / 64);
-    T tl;
-    for (int32_t qi = uni(blockIdx.x * (CWG / 64) + w); qi < nact; qi += nwaves) {
-        // the first round lists every query in order: the list is not read
-        const int32_t b = j0 == 0 ? qi : uni(ws.act[cur][qi]);
-        int32_t anc[3], rel[3];
-        for (int k = 0; k < 3; ++k) {
-            anc[k] = uni(out.anchors[3 * (int64_t)b + k]);
-            rel[k] = uni(out.relations[3 * (int64_t)b + k]);
-        }
-        const int32_t* qb = ws.qf + (int64_t)b * QF;
-        const int32_t staged = uni(qb[6]);
-        if (staged < 0) continue;   // query without a valid positive
-        // this round's draws: [j0, j1) in the first round, else the query's
-        // own range, set by the previous round's selection
-        int32_t qj0 = j0, qj1 = j1;
-        if (j0 < 0) {
-            const int32_t rg = uni(qb[7]);
-            qj0 = range_lo(rg);
-            qj1 = range_hi(rg);
-        }
-        FSet F[3];
-        int32_t sbeg[3], used = 0;
+    int32_t* row = out.negatives + (int64_t)b * p.n_neg;
+    uint32_t mine = 0, again = 0, todo = 0;   // bit k: candidate 64 k + lane
+    {
+        int32_t c[DPW], old[DPW];
 #pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            sbeg[f] = 0;
-            if (f >= Shape<QT>::nf) { F[f] = FSet{nullptr, 0, true}; continue; }
-            const int32_t beg = uni(qb[2 * f]), n = uni(qb[2 * f + 1]) - beg;
-            if (staged >> f & 1) {
-                sbeg[f] = beg;
-                F[f] = FSet{stage + used, n, true};
-                used += n;
-            } else {
-                F[f] = FSet{g.fwd.nbr + beg, n, false};
+        for (int k = 0; k < DPW; ++k) {
+            c[k] = old[k] = -1;
+            if (64 * k >= n) continue;
+            const int32_t i = 64 * k + lane;
+            if (i < n && (L.non[i >> 5] >> (i & 31) & 1u)) {
+                c[k] = L.cand[i];
+                const uint32_t h = table_slot(tcap, c[k]);
+                old[k] = atomicCAS(&tab[h], -1, c[k]);
+                L.sj[i] = (uint16_t)h;   // the survivor list is done with: slots of the values
             }
         }
-        // copy of the staged lists into the wave's LDS slice
-        auto stage_lists = [&]() {
 #pragma unroll
-            for (int f = 0; f < 3; ++f) {
-                if (f >= Shape<QT>::nf || !(staged >> f & 1)) continue;
-                int32_t* dst = stage + (F[f].p - stage);
-                for (int32_t k = lane; k < F[f].n; k += 64) dst[k] = g.fwd.nbr[sbeg[f] + k];
+        for (int k = 0; k < DPW; ++k) {
+            if (c[k] < 0) continue;
+            if (old[k] == -1) mine |= 1u << k;
+            else if (old[k] == c[k]) again |= 1u << k;
+            else todo |= 1u << k;
+        }
+    }
+    while (todo) {
+        const int k = __ffs(todo) - 1, i = 64 * k + lane;
+        const int32_t c = L.cand[i];
+        uint32_t h = L.sj[i];
+        int32_t old;
+        do {
+            h = table_next(tcap, h);
+            old = atomicCAS(&tab[h], -1, c);
+        } while (old != -1 && old != c);
+        L.sj[i] = (uint16_t)h;
+        todo &= todo - 1;
+        if (old == -1) mine |= 1u << k;
+        else again |= 1u << k;
+    }
+    if (__ballot(again != 0)) {
+        // some value was met again (rare): of the window's draws of a value
+        // new to the table the first has it.  Slots of such values hold the
+        // least draw of the value for a moment, as -2 - draw under a
+        // maximum, which leaves the values of earlier windows alone.
+        wave_sync();
+        for (uint32_t m = mine; m; m &= m - 1) tab[L.sj[64 * (__ffs(m) - 1) + lane]] = INT_MIN;
+        wave_sync();
+        const uint32_t all = mine | again;
+        for (uint32_t m = all; m; m &= m - 1) {
+            const int i = 64 * (__ffs(m) - 1) + lane;
+            atomicMax(&tab[L.sj[i]], -2 - i);
+        }
+        wave_sync();
+        mine = 0;
+        for (uint32_t m = all; m; m &= m - 1) {
+            const int k = __ffs(m) - 1, i = 64 * k + lane;
+            if (tab[L.sj[i]] == -2 - i) mine |= 1u << k;
+        }
+        wave_sync();
+        for (uint32_t m = mine; m; m &= m - 1) {
+            const int i = 64 * (__ffs(m) - 1) + lane;
+            tab[L.sj[i]] = L.cand[i];
+        }
+        wave_sync();
+    }
+#pragma unroll
+    for (int k = 0; k < DPW; ++k) {
+        if (64 * k >= n) break;
+        const bool kept = mine >> k & 1;
+        const uint64_t keep = __ballot(kept);
+        const int32_t rank = acc + __popcll(keep & below);
+        if (kept && rank < p.n_neg) {
+            row[rank] = L.cand[64 * k + lane];
+            if (rank == p.n_neg - 1) out.neg_draws[b] = j0 + 64 * k + lane + 1;
+        }
+        acc = uni(min(p.n_neg, acc + __popcll(keep)));
+    }
+    return acc;
+}
+
+// Modes of the candidate kernels: the first kernel of a call, which leaves a
+// query with long lists to the long-list kernels and the finishing kernel;
+// the finishing kernel, which decides everything itself; and given
+// candidates (shared or per query), whose verdicts are packed into mask rows.
+enum : int { DRAW_FIRST = 0, DRAW_FINISH = 1, DRAW_GIVEN = 2 };
+
+// One query on one wavefront.
+template <int QT, class T, int MODE>
+__device__ __forceinline__ void query_draws(const GraphView& g, const SampleParams& p,
+                                            const smore_sample_out& out, const Ws& ws, int64_t* stats,
+                                            uint32_t* mask, const Table& tb, int32_t* own_tab,
+                                            WaveLds& L, int32_t b, int32_t j_first, int lane)
+{
+    const uint64_t below = lanes_below(lane);
+    const int32_t words = (p.n_neg + 31) >> 5;
+    int32_t* qb = ws.qf + (int64_t)b * QF;
+    const int32_t staged = uni(qb[6]);
+    if (staged < 0) {   // query without a valid positive
+        if constexpr (MODE == DRAW_GIVEN)
+            for (int32_t k = lane; k < words; k += 64) mask[(int64_t)b * words + k] = 0;
+        return;
+    }
+    int32_t anc[3], rel[3];
+    for (int k = 0; k < 3; ++k) {
+        anc[k] = uni(out.anchors[3 * (int64_t)b + k]);
+        rel[k] = uni(out.relations[3 * (int64_t)b + k]);
+    }
+    T tl;
+    FList F[3];
+    int32_t used = 0;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+        F[f] = FList{0, 0, 0, false};
+        if (f >= Shape<QT>::nf) continue;
+        F[f].beg = uni(qb[2 * f]);
+        F[f].n = uni(qb[2 * f + 1]) - F[f].beg;
+        F[f].lds = staged >> f & 1;
+        F[f].off = used;
+        if (F[f].lds) used += F[f].n;
+    }
+    // copy of the staged lists into the wave's LDS slice, with their bits
+    auto stage_lists = [&]() {
+        for (int k = lane; k < BIT_WORDS; k += 64) L.bits[k] = 0;
+        wave_sync();
+#pragma unroll
+        for (int f = 0; f < Shape<QT>::nf; ++f) {
+            if (!F[f].lds) continue;
+            for (int32_t k0 = lane; k0 < F[f].n; k0 += 256) {   // four loads in flight
+                int32_t x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    x[u] = k0 + 64 * u < F[f].n ? g.fwd.nbr[F[f].beg + k0 + 64 * u] : -1;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (k0 + 64 * u >= F[f].n) break;
+                    const uint32_t h = bit_slot<QT>(f, x[u]);
+                    L.stage[F[f].off + k0 + 64 * u] = x[u];
+                    atomicOr(&L.bits[h >> 5], 1u << (h & 31));
+                }
+            }
+        }
+        wave_sync();
+    };
+    uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
+    int32_t* tab = tb.own ? own_tab : L.stage;
+    // first test of every draw: the bits of the staged root-edge lists when
+    // the shape has them (LDS only; the survivors are then looked up in the
+    // lists), else the in-edge mask; in the latter case the lists are copied
+    // while the first window's mask words are in flight
+    constexpr int RM = RootLists<QT>::mask;
+    const bool use_lists = RM != 0 && (RootLists<QT>::any ? (staged & RM) == RM : (staged & RM) != 0);
+    // signature bits an answer must carry
+    uint32_t need = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (RootRels<QT>::mask >> k & 1) need |= sig_bit(rel[k]);
+    int32_t acc = 0, base = 0, end = j_first, cnt = 0;
+    bool deferred = false;
+    int32_t steps = MODE == DRAW_FINISH ? INT_MAX : DEEP_STEPS;
+    int32_t jsel = 0;     // draws [0, jsel) are selected
+    if constexpr (MODE == DRAW_FINISH) {
+        // the draws the first kernel left: their states are settled now
+        acc = uni(ws.act[1][b]);
+        const int32_t rg = uni(qb[7]);
+        base = range_lo(rg);
+        end = range_hi(rg);
+        table_fill(tab, tb.tcap, out.negatives + (int64_t)b * p.n_neg, acc, lane);
+        for (; base < end && acc < p.n_neg;) {
+            const int32_t n = min(end - base, min(WIN, table_room(tb.tcap) - acc));
+            for (int k = 0; 64 * k < n; ++k) {
+                const int32_t i = 64 * k + lane;
+                const bool non = i < n && sv[base + i] == ST_NON;
+                const uint64_t m = __ballot(non);
+                if (i < n) L.cand[i] = candidate(p, g.V, b, base + i);
+                if (lane < 2) L.non[2 * k + lane] = (uint32_t)(m >> (32 * lane));
             }
             wave_sync();
-        };
-        uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
-        // first test of every draw: the staged root-edge lists when the
-        // shape has them (LDS only), else the in-edge mask; in the latter
-        // case the lists are copied while the first window's mask words
-        // are in flight
-        constexpr int RM = RootLists<QT>::mask;
-        const bool use_lists = RM != 0 && (RootLists<QT>::any ? (staged & RM) == RM : (staged & RM) != 0);
-        // signature bits an answer must carry
-        uint32_t need = 0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            if (RootRels<QT>::mask >> k & 1) need |= sig_bit(rel[k]);
-        bool to_stage = used > 0;
-        if (use_lists) {
+            acc = select_window(p, out, b, L, tab, tb.tcap, base, n, acc, lane);
+            base += n;
+            wave_sync();
+        }
+        end = acc < p.n_neg ? next_round_end(p, base, acc) : base;
+    }
+    bool to_stage = used > 0;
+    bool table = MODE == DRAW_FINISH && tb.own;   // the table holds the row so far
+    while (base < end) {
+        const int32_t n = MODE == DRAW_GIVEN ? min(end - base, WIN)
+                                             : min(end - base, min(WIN, table_room(tb.tcap) - acc));
+        const int32_t stop = base + n;
+        if (use_lists && to_stage) {
             stage_lists();
             to_stage = false;
         }
-        for (int32_t base = qj0; base < qj1; base += WIN) {
-            // Every answer of every shape is reached by a projection, so a
-            // draw without an in-edge is a non-answer: the in-edge mask (V
-            // bits, resident in the last-level cache) decides most draws.
-            // On a large graph the coarse mask (one bit per four entities,
-            // small enough for the L2) is read first, and only draws whose
-            // group of four has an in-edge read their in-relation
-            // signature (a byte per entity), which must hold the bits of
-            // the relations that end at the root: a draw with in-edges
-            // only under other relation classes is a non-answer too.
-            int32_t c[DPW];
-            uint32_t word[DPW];
-            const bool two_level = !use_lists && g.coarse;
+        // Every answer of every shape is reached by a projection, so a
+        // draw without an in-edge is a non-answer: the in-edge mask (V
+        // bits, resident in the last-level cache) decides most draws.
+        // On a large graph the coarse mask (one bit per four entities,
+        // small enough for the L2) is read first, and only draws whose
+        // group of four has an in-edge read their in-relation
+        // signature (a byte per entity), which must hold the bits of
+        // the relations that end at the root: a draw with in-edges
+        // only under other relation classes is a non-answer too.
+        int32_t c[DPW];
+        uint32_t word[DPW];
+        const bool two_level = !use_lists && g.coarse;
+#pragma unroll
+        for (int k = 0; k < DPW; ++k) {
+            const int32_t j = base + k * 64 + lane;
+            c[k] = -1;
+            word[k] = 0;
+            if (j < stop) {
+                c[k] = candidate(p, g.V, b, j);   // -1 (given candidates only): never a negative
+                if (!use_lists && c[k] >= 0)
+                    word[k] = two_level ? g.has_in4[c[k] >> 7] : g.has_in[c[k] >> 5];
+                L.cand[k * 64 + lane] = c[k];
+            }
+        }
+        if (to_stage) {
+            stage_lists();
+            to_stage = false;
+        }
+        if (two_level) {
 #pragma unroll
             for (int k = 0; k < DPW; ++k) {
-                const int32_t j = base + k * 64 + lane;
-                c[k] = 0;
-                word[k] = 0;
-                if (j < qj1) {
-                    c[k] = candidate(p, g.V, b, j);   // -1 (given candidates only): never a negative
-                    if (!use_lists && c[k] >= 0)
-                        word[k] = two_level ? g.has_in4[c[k] >> 7] : g.has_in[c[k] >> 5];
-                }
+                // accounted as one mask line per draw, as the one-level test
+                const bool live = c[k] >= 0;
+                const bool maybe = live && ((word[k] >> ((c[k] >> 2) & 31)) & 1u);
+                if (live) tl.read(g.has_in4 + (c[k] >> 7), 4);
+                const uint32_t sg = maybe ? (uint32_t)g.sig[c[k]] : 0u;
+                const bool pass = RootRels<QT>::any ? (sg & need) != 0 : (sg & need) == need;
+                word[k] = pass ? ~0u : 0u;
             }
-            if (to_stage) {
-                stage_lists();
-                to_stage = false;
-            }
-            if (two_level) {
-#pragma unroll
-                for (int k = 0; k < DPW; ++k) {
-                    // accounted as one mask line per draw, as the one-level test
-                    const bool live = base + k * 64 + lane < qj1 && c[k] >= 0;
-                    const bool maybe = live && ((word[k] >> ((c[k] >> 2) & 31)) & 1u);
-                    if (live) tl.read(g.has_in4 + (c[k] >> 7), 4);
-                    const uint32_t sg = maybe ? (uint32_t)g.sig[c[k]] : 0u;
-                    const bool pass = RootRels<QT>::any ? (sg & need) != 0 : (sg & need) == need;
-                    word[k] = pass ? ~0u : 0u;
-                }
-            }
-            if (use_lists) {
-#pragma unroll
-                for (int k = 0; k < DPW; ++k) {
-                    if (c[k] < 0) continue;   // (candidates given by the caller only)
-                    bool hit = !RootLists<QT>::any;
-#pragma unroll
-                    for (int f = 0; f < 3; ++f) {
-                        if (!(RM >> f & 1) || !(staged >> f & 1)) continue;
-                        const bool h = has(F[f], c[k], tl);
-                        hit = RootLists<QT>::any ? (hit || h) : (hit && h);
-                    }
-                    word[k] = hit ? ~0u : 0u;
-                }
-            }
-            int32_t nsurv = 0;
+        }
+        if (use_lists) {
 #pragma unroll
             for (int k = 0; k < DPW; ++k) {
-                const int32_t j = base + k * 64 + lane;
-                const bool live = j < qj1;
-                const bool in = live && c[k] >= 0 && ((word[k] >> (c[k] & 31)) & 1u);
-                if (live) {
-                    if (!use_lists && !two_level && c[k] >= 0) tl.read(g.has_in + (c[k] >> 5), 4);
-                    if (!in) sv[j] = c[k] >= 0 ? ST_NON : ST_DUP;   // ST_DUP: not an entity
+                if (c[k] < 0) continue;   // past the window, or not an entity
+                bool hit = !RootLists<QT>::any;
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    if (!(RM >> f & 1) || !F[f].lds) continue;
+                    const bool h = maybe_in<QT>(L, f, c[k]);
+                    hit = RootLists<QT>::any ? (hit || h) : (hit && h);
                 }
-                const uint64_t m = __ballot(in);
-                if (in) {
-                    const int32_t at = nsurv + __popcll(m & below);
-                    sc[at] = c[k];
-                    sj[at] = (uint16_t)j;
-                }
-                nsurv += __popcll(m);
+                word[k] = hit ? ~0u : 0u;
             }
-            wave_sync();
-            // shallow pass over the survivors, 64 at a time; candidates with
-            // a short backward list are collected (in place, over entries
-            // already consumed) for one deep pass, so the dependent steps of
-            // the window's few deep candidates overlap
-            int32_t ndeep = 0;
-            for (int32_t s0 = 0; s0 < nsurv; s0 += 128) {
+        }
+        int32_t nsurv = 0;
+#pragma unroll
+        for (int k = 0; k < DPW; ++k) {
+            const bool live = c[k] >= 0;
+            const bool in = live && ((word[k] >> (c[k] & 31)) & 1u);
+            if (live && !use_lists && !two_level) tl.read(g.has_in + (c[k] >> 5), 4);
+            const uint64_t ml = __ballot(live), m = __ballot(in);
+            if (lane < 2) L.non[2 * k + lane] = (uint32_t)(ml >> (32 * lane));
+            if (in) L.sj[nsurv + __popcll(m & below)] = (uint16_t)(k * 64 + lane);
+            nsurv += __popcll(m);
+        }
+        wave_sync();
+        bool left = false;   // some candidate of this lane is left to the long-list kernels
+        // verdict of candidate i: non-answers keep their bit
+        auto settle = [&](int32_t i, int32_t st) {
+            if (st == ST_NON) return;
+            atomicAnd(&L.non[i >> 5], ~(1u << (i & 31)));
+            if (st == ST_PEND) {
+                left = true;
+                if constexpr (MODE != DRAW_GIVEN) L.cand[i] = ~L.cand[i];
+                if constexpr (MODE != DRAW_FINISH) {
+                    const int32_t slot = atomicAdd(&ws.ctrl[0], 1);   // capacity covers a round
+                    ws.queue[slot] = make_int2(b, base + i);
+                }
+            }
+        };
+        // shallow pass over the survivors, 128 at a time; candidates with a
+        // backward list are collected for the deep pass
+        int32_t ndeep = 0;
+        for (int32_t s0 = 0;; s0 += 128) {
+            if (s0 < nsurv) {
                 bool act[2];
-                int32_t cc[2], jj[2], st[2];
+                int32_t cc[2], ii[2], st[2];
                 int2 lst[2] = {make_int2(0, 0), make_int2(0, 0)};
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int32_t at = s0 + 64 * u + lane;
                     act[u] = at < nsurv;
-                    cc[u] = act[u] ? sc[at] : 0;
-                    jj[u] = act[u] ? sj[at] : 0;
+                    ii[u] = act[u] ? L.sj[at] : 0;
+                    cc[u] = act[u] ? L.cand[ii[u]] : 0;
+                    if (use_lists && act[u]) {
+                        bool hit = !RootLists<QT>::any;
+#pragma unroll
+                        for (int f = 0; f < 3; ++f) {
+                            if (!(RM >> f & 1) || !F[f].lds) continue;
+                            if (RootLists<QT>::any) hit = hit || in_stage(L, F[f], cc[u]);
+                            else hit = hit && in_stage(L, F[f], cc[u]);
+                        }
+                        act[u] = hit;
+                    }
                 }
-                wave_sync();
-                shallow_test2<QT>(g, F, anc, rel, cc, act, st, lst, tl);
+                shallow_test2<QT>(g, L, F, anc, rel, cc, act, st, lst, tl);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    if (act[u] && st[u] != ST_DEEP) {
-                        sv[jj[u]] = (uint8_t)st[u];
-                        if (st[u] == ST_PEND) {
-                            const int32_t slot = atomicAdd(&ws.ctrl[0], 1);   // capacity covers a round
-                            ws.queue[slot] = make_int2(b, jj[u]);
+                    if (act[u] && st[u] != ST_DEEP) settle(ii[u], st[u]);
+                    if constexpr (has_long_lists<QT>) {
+                        const bool deep = act[u] && st[u] == ST_DEEP;
+                        const uint64_t m = __ballot(deep);
+                        if (deep) {
+                            const int32_t at = ndeep + __popcll(m & below);
+                            L.ds[at] = lst[u].x;
+                            L.dl[at] = (uint16_t)min(lst[u].y - lst[u].x, 65535);
+                            L.dj[at] = (uint16_t)ii[u];
                         }
+                        ndeep += __popcll(m);
                     }
-                    const bool deep = act[u] && st[u] == ST_DEEP;
-                    const uint64_t m = __ballot(deep);
-                    if (deep) {
-                        // j < 4096 and 1 <= length <= 8 pack into 15 bits
-                        const int32_t at = ndeep + __popcll(m & below);
-                        sc[at] = lst[u].x;
-                        sj[at] = (uint16_t)((jj[u] << 3) | (lst[u].y - lst[u].x - 1));
+                }
+                wave_sync();
+            }
+            const bool more = s0 + 128 < nsurv;
+            if constexpr (has_long_lists<QT>) {
+                while (ndeep >= 64 || (!more && ndeep > 0)) {   // the newest 64 (at the end: all)
+                    const int32_t d0 = max(0, ndeep - 64), at = d0 + lane;
+                    const bool on = at < ndeep;
+                    uint64_t over;
+                    const uint64_t hit = deep_pass<QT>(g, L, F, rel, on ? L.ds[at] : 0, on ? L.dl[at] : 0,
+                                                       lane, steps, &over, tl);
+                    // pni: a meeting chain means c is in the complemented set
+                    const bool ans = (hit >> lane & 1) != (QT == QPNI);
+                    if (on) settle(L.dj[at], over >> lane & 1 ? ST_PEND : ans ? ST_ANS : ST_NON);
+                    ndeep = d0;
+                }
+                wave_sync();
+            }
+            if (!more) break;
+        }
+        const bool any_left = __ballot(left) != 0;
+        if (MODE == DRAW_FINISH && any_left) {
+            // long lists of the finishing kernel: one after the other, the
+            // whole wavefront on each
+            for (int32_t i0 = 0; i0 < n; i0 += 64) {
+                uint64_t m = __ballot(i0 + lane < n && L.cand[i0 + lane] < 0);
+                for (; m; m &= m - 1) {
+                    const int32_t i = i0 + __ffsll((unsigned long long)m) - 1;
+                    const int32_t c1 = ~uni(L.cand[i]);
+                    T one;
+                    const int2 s = group_range(g.rev, c1, chain_r1<QT> ? rel[1] : rel[2], one);
+                    FSet whole[3];
+#pragma unroll
+                    for (int f = 0; f < 3; ++f) whole[f] = FSet{g.fwd.nbr + F[f].beg, F[f].n};
+                    const bool ans = heavy_test<QT>(g, whole, rel, make_int2(uni(s.x), uni(s.y)), lane, tl);
+                    if (lane == 0) {
+                        L.cand[i] = c1;
+                        if (!ans) L.non[i >> 5] |= 1u << (i & 31);
                     }
-                    ndeep += __popcll(m);
                 }
             }
             wave_sync();
-            for (int32_t d0 = 0; d0 < ndeep; d0 += 64) {
-                if (d0 + lane < ndeep) {
-                    const int32_t start = sc[d0 + lane], pk = sj[d0 + lane];
-                    const int32_t j = pk >> 3;
-                    const int32_t st = deep_test<QT>(g, F, rel, start, (pk & 7) + 1, tl);
-                    sv[j] = (uint8_t)st;
-                    if (st == ST_PEND) {
-                        const int32_t slot = atomicAdd(&ws.ctrl[0], 1);
-                        ws.queue[slot] = make_int2(b, j);
-                    }
-                }
-            }
-            wave_sync();   // the next window reuses the survivor list
         }
-        flush_tally(tl, stats, b, lane);
-        wave_sync();   // the next query restages the wave's slice
+        if constexpr (MODE == DRAW_GIVEN) {
+            const int32_t at = (base >> 5) + lane;
+            const uint32_t bits = lane < WORDS && 32 * lane < n ? L.non[lane] : 0u;
+            if (lane < WORDS && at < words) mask[(int64_t)b * words + at] = bits;
+            cnt += __popc(bits);
+        } else {
+            deferred = deferred || (MODE == DRAW_FIRST && any_left);
+            if (deferred) {
+                for (int32_t i = lane; i < n; i += 64)
+                    sv[base + i] = L.non[i >> 5] >> (i & 31) & 1u ? ST_NON
+                                   : L.cand[i] < 0 ? ST_PEND : ST_ANS;
+            } else {
+                if (!table) table_fill(tab, tb.tcap, out.negatives + (int64_t)b * p.n_neg, acc, lane);
+                table = tb.own;
+                to_stage = used > 0 && !tb.own;   // the table lies over the lists
+                acc = select_window(p, out, b, L, tab, tb.tcap, base, n, acc, lane);
+                jsel = stop;
+                if (acc >= p.n_neg) break;
+            }
+        }
+        base = stop;
+        if (MODE != DRAW_GIVEN && !deferred && base >= end && base < p.neg_tries)
+            end = next_round_end(p, base, acc);
+        wave_sync();   // the next window reuses the lists
+    }
+    if constexpr (MODE == DRAW_GIVEN) {
+        for (int32_t k = ((base + 31) >> 5) + lane; k < words; k += 64) mask[(int64_t)b * words + k] = 0;
+        for (int s = 32; s > 0; s >>= 1) cnt += __shfl_xor(cnt, s);
+        if (lane == 0) out.n_valid[b] = cnt;
+    } else if (deferred) {
+        if (lane == 0) {
+            qb[7] = pack_range(jsel, base);
+            ws.act[1][b] = acc;
+            ws.act[0][atomicAdd(&ws.ctrl[2], 1)] = b;
+        }
+    } else {
+        int32_t* row = out.negatives + (int64_t)b * p.n_neg;
+        for (int32_t k = acc + lane; k < p.n_neg; k += 64) row[k] = -1;
+        if (lane == 0) {
+            out.n_valid[b] = acc;
+            if (acc < p.n_neg) out.neg_draws[b] = p.neg_tries;
+        }
+    }
+    flush_tally(tl, stats, b, lane);
+}
+
+// One query per workgroup: queries differ widely in cost, and the hardware
+// dispatcher hands each freed slot the next query.
+template <int QT, class T>
+__global__ __launch_bounds__(CWG, 4) void k_candidates(GraphView g, SampleParams p, smore_sample_out out,
+                                                    Ws ws, int64_t* stats, Table tb, int32_t j_first)
+{
+    __shared__ WaveLds L;
+    extern __shared__ __align__(16) int32_t own_tab[];
+    query_draws<QT, T, DRAW_FIRST>(g, p, out, ws, stats, nullptr, tb, own_tab, L, blockIdx.x, j_first,
+                                   threadIdx.x);
+}
+
+// Given candidates (p.shared): mask rows and counts of the pairs.
+template <int QT>
+__global__ __launch_bounds__(CWG, 4) void k_pairs(GraphView g, SampleParams p, smore_sample_out out, Ws ws,
+                                               uint32_t* mask)
+{
+    __shared__ WaveLds L;
+    const int32_t n = p.n_shared ? min(p.n_neg, uni(*p.n_shared)) : p.n_neg;
+    query_draws<QT, NoTally, DRAW_GIVEN>(g, p, out, ws, nullptr, mask, Table{0, 0}, nullptr, L,
+                                         blockIdx.x, n, threadIdx.x);
+}
+
+// The queries that had long lists among their first draws, once those are
+// settled: selection, and whatever further draws they need.  Persistent
+// one-wave workgroups over the list.
+template <int QT, class T>
+__global__ __launch_bounds__(CWG, 4) void k_finish(GraphView g, SampleParams p, smore_sample_out out, Ws ws,
+                                                int64_t* stats, Table tb)
+{
+    __shared__ WaveLds L;
+    extern __shared__ __align__(16) int32_t own_tab[];
+    const int32_t n = uni(ws.ctrl[2]);
+    for (int32_t qi = blockIdx.x; qi < n; qi += gridDim.x) {
+        query_draws<QT, T, DRAW_FINISH>(g, p, out, ws, stats, nullptr, tb, own_tab, L,
+                                        uni(ws.act[0][qi]), 0, threadIdx.x);
+        wave_sync();
+    }
+}
+
+// Verdict of a queued pair by the long-list kernels: its state, or for given
+// candidates (mask not NULL) its bit of the mask row and the row's count.
+__device__ __forceinline__ void put_verdict(const SampleParams& p, const smore_sample_out& out,
+                                            const Ws& ws, uint32_t* mask, int32_t b, int32_t j, bool ans)
+{
+    if (!mask) {
+        ws.status[(int64_t)b * p.neg_tries + j] = ans ? ST_ANS : ST_NON;
+    } else {
+        uint32_t* w = mask + (int64_t)b * ((p.n_neg + 31) >> 5) + (j >> 5);
+        const uint32_t bit = 1u << (j & 31);
+        if (ans) {
+            if (atomicAnd(w, ~bit) & bit) atomicSub(&out.n_valid[b], 1);
+        } else {
+            if (!(atomicOr(w, bit) & bit)) atomicAdd(&out.n_valid[b], 1);
+        }
     }
 }
 
@@ -1362,20 +1798,17 @@ __global__ __launch_bounds__(CWG) void k_candidates(GraphView g, SampleParams p,
 // so those dependent reads overlap instead of preceding each test in turn.
 template <int QT, class T>
 __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p, smore_sample_out out,
-                                                    Ws ws, int64_t* stats, int nxt)
+                                                    Ws ws, int64_t* stats, uint32_t* mask)
 {
     constexpr int NF = Shape<QT>::nf;
     const int lane = threadIdx.x & 63;
-    // the compaction that follows appends to the next round's list
-    if (blockIdx.x == 0 && threadIdx.x == 0) ws.ctrl[2 + nxt] = 0;
     const int32_t total = uni(ws.ctrl[0]);
     const int32_t nwaves = gridDim.x * (HEAVY_WG / 64);
     const int32_t w0 = uni(blockIdx.x * (HEAVY_WG / 64) + (threadIdx.x >> 6));
     T tl;
     for (int64_t base = w0; base < total; base += 64 * (int64_t)nwaves) {
         const int64_t mine = base + (int64_t)lane * nwaves;
-        int32_t mb = 0, mc = 0;
-        int64_t mat = 0;
+        int32_t mb = 0, mc = 0, mj = 0;
         int32_t mrel[3] = {0, 0, 0}, mf[2 * NF];
         int2 ms = make_int2(0, 0);
 #pragma unroll
@@ -1383,7 +1816,7 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p,
         if (mine < total) {
             const int2 it = ws.queue[mine];
             mb = it.x;
-            mat = (int64_t)it.x * p.neg_tries + it.y;
+            mj = it.y;
             mc = candidate(p, g.V, it.x, it.y);
 #pragma unroll
             for (int k = 0; k < 3; ++k) mrel[k] = out.relations[3 * (int64_t)mb + k];
@@ -1403,9 +1836,9 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p,
             for (int f = 0; f < 3; ++f) {
                 if (f < NF) {
                     const int32_t beg = readlane(mf[2 * f], k), end = readlane(mf[2 * f + 1], k);
-                    F[f] = FSet{g.fwd.nbr + beg, end - beg, false};
+                    F[f] = FSet{g.fwd.nbr + beg, end - beg};
                 } else {
-                    F[f] = FSet{nullptr, 0, true};
+                    F[f] = FSet{nullptr, 0};
                 }
             }
             if constexpr (T::on) {
@@ -1416,36 +1849,10 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p,
             }
             const int2 s = make_int2(readlane(ms.x, k), readlane(ms.y, k));
             const bool ans = heavy_test<QT>(g, F, rel, s, lane, tl);
-            if (lane == 0) ws.status[readlane64(mat, k)] = ans ? ST_ANS : ST_NON;
+            if (lane == 0) put_verdict(p, out, ws, mask, b, readlane(mj, k), ans);
             flush_tally(tl, stats, b, lane, 2);
         }
     }
-}
-
-// Highest lane whose exclusive prefix excl is <= idx (binary lifting over
-// the wavefront; every lane must be active).  excl is nondecreasing over
-// the lanes and 0 in lane 0.
-__device__ __forceinline__ int owner_lane(int32_t idx, int32_t excl)
-{
-    int lo = 0;
-#pragma unroll
-    for (int step = 32; step >= 1; step >>= 1) {
-        const int cand = lo + step;
-        const int32_t ev = __shfl(excl, cand > 63 ? 63 : cand);
-        if (cand <= 63 && ev <= idx) lo = cand;
-    }
-    return lo;
-}
-
-__device__ __forceinline__ int32_t excl_prefix(int32_t v, int lane, int32_t* total)
-{
-    int32_t incl = v;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-    }
-    *total = uni(__shfl(incl, 63));
-    return incl - v;
 }
 
 // OR of a 64-bit value over the wavefront.
@@ -1458,15 +1865,14 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t x)
 }
 
 // A slice of one queued 3p item, held by one lane: the item's draw (its
-// query b and state index mat), relation r1, forward list F0 = A_r0(a0)
+// query b and index j), relation r1, forward list F0 = A_r0(a0)
 // (edges [f0b, f0b + f0n)), the candidate's list S = R_r2(c) (edges from
 // sx), the range [y0, y1) of S's entities to expand and, for each of them,
 // the range [k0, k1) of its (y, key) pairs to search (keys from the shorter
 // of R_r1(y) and F0).
 struct Slice3 {
     bool valid = false;
-    int32_t b = -1;
-    int64_t mat = 0;
+    int32_t b = -1, j = 0;
     int32_t r1 = 0, f0b = 0, f0n = 0, sx = 0, y0 = 0, y1 = 0, k0 = 0, k1 = 0;
 };
 
@@ -1608,7 +2014,7 @@ __device__ __forceinline__ Slice3 item_slice3(const GraphView& g, const SamplePa
     const int2 it = ws.queue[qi];
     w.valid = true;
     w.b = it.x;
-    w.mat = (int64_t)it.x * p.neg_tries + it.y;
+    w.j = it.y;
     const int32_t c = candidate(p, g.V, it.x, it.y);
     w.r1 = out.relations[3 * (int64_t)w.b + 1];
     const int32_t r2 = out.relations[3 * (int64_t)w.b + 2];
@@ -1633,10 +2039,9 @@ __device__ __forceinline__ Slice3 item_slice3(const GraphView& g, const SamplePa
 // queries are exact).
 template <class T>
 __global__ __launch_bounds__(HEAVY_WG) void k_heavy3(GraphView g, SampleParams p, smore_sample_out out,
-                                                     Ws ws, int64_t* stats, int nxt)
+                                                     Ws ws, int64_t* stats, uint32_t* mask)
 {
     const int lane = threadIdx.x & 63;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ws.ctrl[2 + nxt] = 0;
     const int32_t total = uni(ws.ctrl[0]);
     const int32_t nwaves = gridDim.x * (HEAVY_WG / 64);
     const int32_t w0 = uni(blockIdx.x * (HEAVY_WG / 64) + (threadIdx.x >> 6));
@@ -1646,9 +2051,18 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy3(GraphView g, SampleParams p
         Slice3 w;
         if (mine < total) w = item_slice3(g, p, out, ws, mine, tl);
         const uint64_t ans = decide_slices3<true>(g, ws, w, mine, lane, tl);
-        if (mine < total) ws.status[w.mat] = ((ans >> lane) & 1) ? ST_ANS : ST_NON;
+        if (mine < total) put_verdict(p, out, ws, mask, w.b, w.j, (ans >> lane) & 1);
         flush_tally(tl, stats, uni(__shfl(w.b, 0)), lane, 2);
     }
+}
+
+// Is the queued pair already an answer?  (Every queued pair has had a
+// verdict from the long-list kernel before.)
+__device__ __forceinline__ bool is_answer(const SampleParams& p, const Ws& ws, const uint32_t* mask,
+                                          int32_t b, int32_t j)
+{
+    if (!mask) return ws.status[(int64_t)b * p.neg_tries + j] == ST_ANS;
+    return !(mask[(int64_t)b * ((p.n_neg + 31) >> 5) + (j >> 5)] >> (j & 31) & 1u);
 }
 
 // The units the long-list kernel left: wavefront w takes units w,
@@ -1657,7 +2071,7 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy3(GraphView g, SampleParams p
 // (units never clear a state, so their order does not matter).
 template <class T>
 __global__ __launch_bounds__(HEAVY_WG) void k_units3(GraphView g, SampleParams p, smore_sample_out out,
-                                                     Ws ws, int64_t* stats)
+                                                     Ws ws, int64_t* stats, uint32_t* mask)
 {
     const int lane = threadIdx.x & 63;
     const int32_t total = uni((int32_t)min((int64_t)ws.ctrl[5], ws.ucap));
@@ -1671,7 +2085,7 @@ __global__ __launch_bounds__(HEAVY_WG) void k_units3(GraphView g, SampleParams p
             const int4 u = ws.units[mine];
             if (u.w != 2) {
                 w = item_slice3(g, p, out, ws, u.x, tl);
-                if (ws.status[w.mat] == ST_ANS) {
+                if (is_answer(p, ws, mask, w.b, w.j)) {
                     w.valid = false;
                 } else if (u.w == 0) {           // entities [a, b) of S, all keys
                     w.y0 = u.y;
@@ -1685,7 +2099,7 @@ __global__ __launch_bounds__(HEAVY_WG) void k_units3(GraphView g, SampleParams p
             }
         }
         const uint64_t ans = decide_slices3<false>(g, ws, w, -1, lane, tl);
-        if (w.valid && ((ans >> lane) & 1)) ws.status[w.mat] = ST_ANS;
+        if (w.valid && ((ans >> lane) & 1)) put_verdict(p, out, ws, mask, w.b, w.j, true);
         flush_tally(tl, stats, uni(__shfl(max(w.b, 0), 0)), lane, 2);
     }
 }
@@ -1712,213 +2126,24 @@ __device__ __forceinline__ int32_t ht_first(const int32_t* tv, const int32_t* tj
     return tj[h];
 }
 
-// Per active query, one wavefront per query (one-wave workgroups; the LDS
-// holds the round's first-occurrence table and the query's draws and
-// states): keep draw j iff it is not an answer and no earlier draw has the
-// same value; the first n_neg kept, in draw order, are the negatives.
-// Queries neither complete nor out of budget go to the next round's list
-// with their next draw range (next_round_end).
-__global__ __launch_bounds__(64) void k_compact(SampleParams p, int32_t V, smore_sample_out out, Ws ws,
-                                                int cur, int32_t j_end, int last, int next_last,
-                                                int32_t tcap, int tshift, int ident)
-{
-    extern __shared__ int32_t lds[];
-    int32_t* tv = lds;
-    int32_t* tj = lds + tcap;
-    int32_t* vals = lds + 2 * tcap;
-    uint8_t* sts = (uint8_t*)(vals + j_end);
-    const int lane = threadIdx.x;
-    const uint64_t below = lanes_below(lane);
-    const uint32_t tmask = (uint32_t)tcap - 1;
-    const int32_t nact = uni(ws.ctrl[2 + cur]);
-    // the heavy queue of this round is drained: ready it for the next round
-    if (blockIdx.x == 0 && lane == 0) { ws.ctrl[0] = 0; ws.ctrl[1] = 0; ws.ctrl[5] = 0; }
-    for (int32_t qi = blockIdx.x; qi < nact; qi += gridDim.x) {
-        const int32_t b = uni(ws.act[cur][qi]);
-        if (uni(ws.qf[(int64_t)b * QF + 6]) < 0) continue;   // query without a valid positive
-        // the query's draws so far (at most j_end, which sizes the LDS)
-        const int32_t jq = ident ? j_end : range_hi(uni(ws.qf[(int64_t)b * QF + 7]));
-        const uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
-        int32_t* row = out.negatives + (int64_t)b * p.n_neg;
-        for (int32_t k = lane; k < tcap; k += 64) { tv[k] = -1; tj[k] = INT_MAX; }
-        for (int32_t j = lane; j < jq; j += 64) {
-            vals[j] = candidate(p, V, b, j);
-            sts[j] = sv[j];
-        }
-        wave_sync();
-        for (int32_t j = lane; j < jq; j += 64) ht_insert(tv, tj, tmask, tshift, vals[j], j);
-        wave_sync();
-        int32_t acc = 0;
-        for (int32_t row0 = 0; row0 < jq && acc < p.n_neg; row0 += 64) {
-            const int32_t j = row0 + lane;
-            int32_t c = 0;
-            bool keep = false;
-            if (j < jq) {
-                c = vals[j];
-                keep = sts[j] == ST_NON && ht_first(tv, tj, tmask, tshift, c) == j;
-            }
-            const uint64_t m = __ballot(keep);
-            const int32_t rank = acc + __popcll(m & below);
-            if (keep && rank < p.n_neg) {
-                row[rank] = c;
-                if (rank == p.n_neg - 1) out.neg_draws[b] = j + 1;
-            }
-            acc = uni(min(p.n_neg, acc + __popcll(m)));
-        }
-        if (acc == p.n_neg || last || jq >= p.neg_tries) {
-            for (int32_t k = acc + lane; k < p.n_neg; k += 64) row[k] = -1;
-            if (lane == 0) {
-                out.n_valid[b] = acc;
-                if (acc < p.n_neg) out.neg_draws[b] = p.neg_tries;
-            }
-        } else if (lane == 0) {
-            ws.qf[(int64_t)b * QF + 7] = pack_range(jq, next_round_end(p, jq, acc, next_last));
-            ws.act[cur ^ 1][atomicAdd(&ws.ctrl[2 + (cur ^ 1)], 1)] = b;
-        }
-        wave_sync();
-    }
-}
-
-// The same selection for rounds of at most 64 * CK draws, with every load
-// in flight at once: each lane holds its CK draws (j = lane + 64 k) in
-// registers, one wavefront per query, four per workgroup, and only the
-// hash table lives in LDS.  Only non-answers enter the table: a value's
-// state is the same at each of its occurrences, so the first non-answer
-// occurrence of a value is its first occurrence.
-constexpr int CK = 16;
-constexpr int CWAVES = 4;
-
-// One wavefront per listed query; its states are read in one round trip
-// while its draws are recomputed (the first round lists every query in
-// order, so the list itself is not read then, and the query's validity flag
-// is loaded beside the states rather than before them).
-template <int NK>
-__global__ __launch_bounds__(64 * CWAVES) void k_compact_reg(SampleParams p, int32_t V,
-                                                             smore_sample_out out, Ws ws, int cur,
-                                                             int32_t j_end, int last, int next_last,
-                                                             int32_t tcap, int tshift, int ident)
-{
-    extern __shared__ int32_t lds[];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int32_t* tv = lds + (size_t)w * tcap;
-    const uint64_t below = lanes_below(lane);
-    const uint32_t tmask = (uint32_t)tcap - 1;
-    const int32_t nact = uni(ws.ctrl[2 + cur]);
-    if (blockIdx.x == 0 && threadIdx.x == 0) { ws.ctrl[0] = 0; ws.ctrl[1] = 0; ws.ctrl[5] = 0; }
-    for (int32_t qi = uni(blockIdx.x * CWAVES + w); qi < nact; qi += gridDim.x * CWAVES) {
-        const int32_t b = ident ? qi : uni(ws.act[cur][qi]);
-        const int32_t flag = ws.qf[(int64_t)b * QF + 6];   // < 0: query without a valid positive
-        // the query's draws so far: all of the first round, or up to the end
-        // of its own range in a later one
-        const int32_t jq = ident ? j_end : range_hi(uni(ws.qf[(int64_t)b * QF + 7]));
-        const int32_t nk = uni((jq + 63) >> 6);
-        const uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
-        int32_t* row = out.negatives + (int64_t)b * p.n_neg;
-        int32_t c[NK];
-        uint8_t st[NK];
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            const int32_t j = 64 * k + lane;
-            c[k] = -1;
-            st[k] = ST_ANS;
-            if (k < nk && j < jq) st[k] = sv[j];
-        }
-        // the draws themselves are recomputed while the states are in flight
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            const int32_t j = 64 * k + lane;
-            if (k < nk && j < jq) c[k] = candidate(p, V, b, j);
-        }
-        if (uni(flag) < 0) continue;
-        bool non[NK];
-#pragma unroll
-        for (int k = 0; k < NK; ++k) non[k] = st[k] == ST_NON;
-        int4* t4 = (int4*)tv;
-        for (int32_t k = lane; k < tcap / 4; k += 64) t4[k] = make_int4(-1, -1, -1, -1);
-        wave_sync();
-        // insert every non-answer's value; first probes of every draw in
-        // flight together, collisions probe on.  A draw that meets its own
-        // value in the table has an equal draw (which of the two came first
-        // is settled below); slots are never emptied, so two equal values
-        // always end in the same slot and one of them meets the other.
-        uint32_t h[NK];
-        int32_t old[NK];
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            h[k] = ((uint32_t)c[k] * 0x9E3779B1u) >> tshift;
-            old[k] = non[k] ? atomicCAS(&tv[h[k]], -1, c[k]) : -1;
-        }
-        bool dup = false;
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            if (!non[k]) continue;
-            uint32_t at = h[k];
-            int32_t o = old[k];
-            while (o != -1 && o != c[k]) {
-                at = (at + 1) & tmask;
-                o = atomicCAS(&tv[at], -1, c[k]);
-            }
-            h[k] = at;
-            dup = dup || o == c[k];
-        }
-        int32_t first[NK];
-#pragma unroll
-        for (int k = 0; k < NK; ++k) first[k] = non[k] ? 64 * k + lane : -1;
-        if (__ballot(dup)) {
-            // some value was drawn twice (rare): the first draw of each
-            // value is the least draw index over its slot (one slot per
-            // value, reused for the minimum)
-#pragma unroll
-            for (int k = 0; k < NK; ++k)
-                if (non[k]) tv[h[k]] = INT_MAX;
-            wave_sync();
-#pragma unroll
-            for (int k = 0; k < NK; ++k)
-                if (non[k]) atomicMin(&tv[h[k]], 64 * k + lane);
-            wave_sync();
-#pragma unroll
-            for (int k = 0; k < NK; ++k) first[k] = non[k] ? tv[h[k]] : -1;
-        }
-        int32_t acc = 0;
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            if (k >= nk || acc >= p.n_neg) break;
-            const int32_t j = 64 * k + lane;
-            const bool keep = non[k] && first[k] == j;
-            const uint64_t m = __ballot(keep);
-            const int32_t rank = acc + __popcll(m & below);
-            if (keep && rank < p.n_neg) {
-                row[rank] = c[k];
-                if (rank == p.n_neg - 1) out.neg_draws[b] = j + 1;
-            }
-            acc = uni(min(p.n_neg, acc + __popcll(m)));
-        }
-        if (acc == p.n_neg || last || jq >= p.neg_tries) {
-            for (int32_t k = acc + lane; k < p.n_neg; k += 64) row[k] = -1;
-            if (lane == 0) {
-                out.n_valid[b] = acc;
-                if (acc < p.n_neg) out.neg_draws[b] = p.neg_tries;
-            }
-        } else if (lane == 0) {
-            ws.qf[(int64_t)b * QF + 7] = pack_range(jq, next_round_end(p, jq, acc, next_last));
-            ws.act[cur ^ 1][atomicAdd(&ws.ctrl[2 + (cur ^ 1)], 1)] = b;
-        }
-        wave_sync();   // the next query clears the table
-    }
-}
-
-// first-occurrence table of the compaction: load factor at most 0.6
-inline int32_t compact_tcap(int32_t j_end)
+// first-occurrence table of the shared set: load factor at most 0.6
+inline int32_t shared_tcap(int32_t j_end)
 {
     int32_t tcap = 64;
     while (tcap * 3 < 5 * j_end) tcap <<= 1;
     return tcap;
 }
 
-// table (value, first draw) + the query's draws and states
-inline size_t compact_lds(int32_t j_end)
+// Selection table of a call.  A row whose first draws are one window has it
+// over the staged lists and their bits (which are copied again if a later
+// window is needed), half empty where there is room; a longer row, with
+// windows that follow one another, in LDS of its own.  Both hold n_neg
+// values and at least 128 more.
+inline Table selection_table(const SampleParams& p)
 {
-    return (size_t)2 * compact_tcap(j_end) * sizeof(int32_t) + (size_t)j_end * 5 + 16;
+    auto blocks = [](int32_t x) { return (x + 255) / 256 * 256; };
+    if (first_round(p) <= WIN) return Table{min(blocks(2 * (p.n_neg + 128)), TABLE_OVER), 0};
+    return Table{blocks(3 * (p.n_neg + WIN) / 2), 1};
 }
 
 inline int check_launch(const char** err)
@@ -1939,17 +2164,36 @@ thread_local ProfileArm g_prof[3];
 // right before the first candidate kernel, after the preparation.
 thread_local hipEvent_t g_wait = nullptr;
 
-inline void prof_mark(int which, int round, bool after, hipStream_t st)
+inline void prof_mark(int which, bool after, hipStream_t st)
 {
     ProfileArm& a = g_prof[which];
-    if (round != 0 || !a.start || !a.stop) return;
+    if (!a.start || !a.stop) return;
     (void)hipEventRecord(after ? a.stop : a.start, st);
     if (after) a = ProfileArm{};
 }
 
-// parts: NEG_PREPARE the per-query preparation, NEG_CANDIDATES the first
-// round's candidate kernel, NEG_REST the first round's long-list and
-// selection kernels and every later round.
+// The long-list kernels over the queue (mask: see put_verdict).
+template <int QT, class T>
+int launch_long_lists(const GraphView& gv, const SampleParams& p, const smore_sample_out& out, Ws ws,
+                      int64_t* stats, uint32_t* mask, hipStream_t st, const char** err)
+{
+    int rc;
+    if constexpr (QT == Q3P) {
+        // a quarter grid: these waves mostly wait on dependent reads, and at
+        // four waves per SIMD a full grid would hold the registers that the
+        // candidate kernels of shapes sampled beside this one need
+        const int grid = mask ? PERSIST_BLOCKS : PERSIST_BLOCKS / 4;
+        k_heavy3<T><<<grid, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, mask);
+        if ((rc = check_launch(err))) return rc;
+        k_units3<T><<<grid, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, mask);
+    } else {
+        k_heavy<QT, T><<<PERSIST_BLOCKS, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, mask);
+    }
+    return check_launch(err);
+}
+
+// parts: NEG_PREPARE the per-query preparation, NEG_CANDIDATES the candidate
+// kernel, NEG_REST the long-list and finishing kernels.
 template <int QT, class T>
 int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample_out& out, Ws ws,
                   int64_t* stats, int32_t R, int parts, hipStream_t st, const char** err)
@@ -1964,80 +2208,32 @@ int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample
         k_prepare<QT, T><<<(p.batch + 63) / 64, 256, 0, st>>>(gv, p, out, ws, stats, R);
         if ((rc = check_launch(err))) return rc;
     }
-    const int rounds = n_rounds(p);
-    for (int r = 0; r < rounds; ++r) {
-        const int cur = r & 1;
-        // the first round's draws are the same for every query; a later
-        // round's are each query's own (j0 = -1), ending at most at neg_tries
-        const int32_t j0 = r == 0 ? 0 : -1;
-        const int32_t j_end = r == 0 ? first_round(p) : p.neg_tries;
-        // later rounds carry the few queries short of n_neg: a smaller grid
-        // keeps their (often empty) launches cheap
-        const int grid = r == 0 ? PERSIST_BLOCKS : PERSIST_BLOCKS / 4;
-        const int cgrid = r == 0 ? max(p.batch, 1) : PERSIST_BLOCKS;   // one-wave workgroups
-        if (parts & (r == 0 ? NEG_CANDIDATES : NEG_REST)) {
-            if (r == 0 && g_wait) {
-                const hipError_t e = hipStreamWaitEvent(st, g_wait, 0);
-                g_wait = nullptr;
-                if (e != hipSuccess) { *err = hipGetErrorString(e); return SMORE_E_HIP; }
-            }
-            prof_mark(0, r, false, st);
-            k_candidates<QT, T><<<cgrid, CWG, 0, st>>>(gv, p, out, ws, stats, cur, j0, j_end);
-            if ((rc = check_launch(err))) return rc;
-            prof_mark(0, r, true, st);
-        }
-        if (!(parts & NEG_REST)) continue;
-        prof_mark(1, r, false, st);
-        if constexpr (QT == Q3P) {
-            // a quarter grid in every round: these waves mostly wait on
-            // dependent reads, and at four waves per SIMD a full grid would
-            // hold the registers that the candidate kernels of shapes sampled
-            // beside this one need
-            k_heavy3<T><<<PERSIST_BLOCKS / 4, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, cur ^ 1);
-            if ((rc = check_launch(err))) return rc;
-            k_units3<T><<<PERSIST_BLOCKS / 4, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats);
-        } else {
-            k_heavy<QT, T><<<grid, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, cur ^ 1);
-        }
-        if ((rc = check_launch(err))) return rc;
-        prof_mark(1, r, true, st);
-        if (j_end <= 64 * CK) {
-            // value table only, at load factor at most 0.3 (short probe chains)
-            const int32_t tcap = compact_tcap(2 * j_end);
-            int tshift = 32;
-            for (int32_t x = tcap; x > 1; x >>= 1) --tshift;
-            prof_mark(2, r, false, st);
-            const size_t tab = (size_t)CWAVES * tcap * sizeof(int32_t);
-            if (j_end <= 64 * 9)
-                k_compact_reg<9><<<grid, 64 * CWAVES, tab, st>>>(p, gv.V, out, ws, cur, j_end,
-                                                                 r == rounds - 1, r + 1 == rounds - 1,
-                                                                 tcap, tshift, r == 0);
-            else
-                k_compact_reg<CK><<<grid, 64 * CWAVES, tab, st>>>(p, gv.V, out, ws, cur, j_end,
-                                                                  r == rounds - 1, r + 1 == rounds - 1,
-                                                                  tcap, tshift, r == 0);
-            if ((rc = check_launch(err))) return rc;
-            prof_mark(2, r, true, st);
-            continue;
-        }
-        const int32_t tcap = compact_tcap(j_end);
-        int tshift = 32;
-        for (int32_t x = tcap; x > 1; x >>= 1) --tshift;
-        const size_t lds = compact_lds(j_end);
-        static bool attr = false;
-        if (lds > 65536 && !attr) {
-            const hipError_t e = hipFuncSetAttribute((const void*)k_compact,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)compact_lds(SMORE_MAX_NEG_TRIES));
+    const Table tb = selection_table(p);
+    const size_t own = tb.own ? (size_t)tb.tcap * sizeof(int32_t) : 0;
+    if (parts & NEG_CANDIDATES) {
+        if (g_wait) {
+            const hipError_t e = hipStreamWaitEvent(st, g_wait, 0);
+            g_wait = nullptr;
             if (e != hipSuccess) { *err = hipGetErrorString(e); return SMORE_E_HIP; }
-            attr = true;
         }
-        prof_mark(2, r, false, st);
-        k_compact<<<grid * 4, 64, lds, st>>>(p, gv.V, out, ws, cur, j_end, r == rounds - 1,
-                                             r + 1 == rounds - 1, tcap, tshift, r == 0);
+        prof_mark(0, false, st);
+        k_candidates<QT, T><<<p.batch, CWG, own, st>>>(gv, p, out, ws, stats, tb, first_round(p));
         if ((rc = check_launch(err))) return rc;
-        prof_mark(2, r, true, st);
+        prof_mark(0, true, st);
     }
+    if (!(parts & NEG_REST)) return SMORE_OK;
+    prof_mark(1, false, st);
+    if constexpr (has_long_lists<QT>) {
+        if ((rc = launch_long_lists<QT, T>(gv, p, out, ws, stats, nullptr, st, err))) return rc;
+    }
+    prof_mark(1, true, st);
+    prof_mark(2, false, st);
+    if constexpr (has_long_lists<QT>) {
+        k_finish<QT, T><<<p.batch < FINISH_BLOCKS ? p.batch : FINISH_BLOCKS, CWG, own, st>>>(gv, p, out, ws,
+                                                                                            stats, tb);
+        if ((rc = check_launch(err))) return rc;
+    }
+    prof_mark(2, true, st);
     return SMORE_OK;
 }
 
@@ -2110,39 +2306,11 @@ __global__ __launch_bounds__(SSET_WG) void k_shared_set(SampleParams p, int32_t 
     if (tid == 0) *n_shared = acc;
 }
 
-// Mask rows from the pair states: bit k of row b set iff state (b, k) is a
-// non-answer; n_valid = set bits.  One wavefront per query.
-__global__ __launch_bounds__(256) void k_pack(SampleParams p, Ws ws, uint32_t* mask, int32_t* n_valid)
-{
-    const int lane = threadIdx.x & 63;
-    const int32_t words = (p.n_neg + 31) >> 5;
-    const int32_t ns = p.n_shared ? uni(*p.n_shared) : p.n_neg;
-    const int32_t nwaves = gridDim.x * 4;
-    for (int32_t b = uni(blockIdx.x * 4 + (threadIdx.x >> 6)); b < p.batch; b += nwaves) {
-        uint32_t* row = mask + (int64_t)b * words;
-        const bool valid = uni(ws.qf[(int64_t)b * QF + 6]) >= 0;
-        const uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
-        int32_t cnt = 0;
-        for (int32_t wd = lane; wd < words; wd += 64) {
-            uint32_t bits = 0;
-            if (valid)
-                for (int k = 0; k < 32; ++k) {
-                    const int32_t j = wd * 32 + k;
-                    if (j < ns && sv[j] == ST_NON) bits |= 1u << k;
-                }
-            row[wd] = bits;
-            cnt += __popc(bits);
-        }
-        for (int s = 32; s > 0; s >>= 1) cnt += __shfl_xor(cnt, s);
-        if (valid && lane == 0) n_valid[b] = cnt;
-    }
-}
-
 // The minibatch's shared candidate set (one workgroup).
 int draw_shared_set(const SampleParams& p, int32_t V, int32_t* shared, int32_t* n_shared,
                     hipStream_t st, const char** err)
 {
-    const int32_t tcap = compact_tcap(p.neg_tries > 0 ? p.neg_tries : 1);
+    const int32_t tcap = shared_tcap(p.neg_tries > 0 ? p.neg_tries : 1);
     int tshift = 32;
     for (int32_t x = tcap; x > 1; x >>= 1) --tshift;
     // the table needs up to 64 KiB plus the counts: raise the kernel's LDS
@@ -2150,7 +2318,7 @@ int draw_shared_set(const SampleParams& p, int32_t V, int32_t* shared, int32_t* 
     const size_t lds = ((size_t)2 * tcap + SSET_WG / 64) * sizeof(int32_t);
     static bool attr = false;
     if (!attr) {
-        const size_t most = ((size_t)2 * compact_tcap(SMORE_MAX_NEG_TRIES) + SSET_WG / 64) * sizeof(int32_t);
+        const size_t most = ((size_t)2 * shared_tcap(SMORE_MAX_NEG_TRIES) + SSET_WG / 64) * sizeof(int32_t);
         const hipError_t e = hipFuncSetAttribute((const void*)k_shared_set,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e != hipSuccess) { *err = hipGetErrorString(e); return SMORE_E_HIP; }
@@ -2173,20 +2341,11 @@ int run_pairs(const GraphView& gv, const SampleParams& p, const smore_sample_out
     }
     k_prepare<QT, NoTally><<<(p.batch + 63) / 64, 256, 0, st>>>(gv, p, q, ws, nullptr, R);
     if ((rc = check_launch(err))) return rc;
-    k_candidates<QT, NoTally, true><<<max(p.batch, 1), CWG, 0, st>>>(gv, p, q, ws, nullptr, 0, 0,
-                                                                     p.n_neg);
+    k_pairs<QT><<<p.batch, CWG, 0, st>>>(gv, p, q, ws, mask);
     if ((rc = check_launch(err))) return rc;
-    if constexpr (QT == Q3P) {
-        k_heavy3<NoTally><<<PERSIST_BLOCKS, HEAVY_WG, 0, st>>>(gv, p, q, ws, nullptr, 1);
-        if ((rc = check_launch(err))) return rc;
-        k_units3<NoTally><<<PERSIST_BLOCKS, HEAVY_WG, 0, st>>>(gv, p, q, ws, nullptr);
-    } else {
-        k_heavy<QT, NoTally><<<PERSIST_BLOCKS, HEAVY_WG, 0, st>>>(gv, p, q, ws, nullptr, 1);
-    }
-    if ((rc = check_launch(err))) return rc;
-    k_pack<<<(p.batch + 3) / 4 < PERSIST_BLOCKS ? (p.batch + 3) / 4 : PERSIST_BLOCKS, 256, 0, st>>>(
-        p, ws, mask, q.n_valid);
-    return check_launch(err);
+    if constexpr (has_long_lists<QT>)
+        return launch_long_lists<QT, NoTally>(gv, p, q, ws, nullptr, mask, st, err);
+    return SMORE_OK;
 }
 
 int dispatch_pairs(QType qt, const GraphView& gv, const SampleParams& p, const smore_sample_out& q,

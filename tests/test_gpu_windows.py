@@ -1,0 +1,66 @@
+"""GPU parity at the edges of the candidate kernel's windows and limits.
+
+A query is one wavefront that draws, verifies and selects window after
+window; lists it must not walk itself go to the long-list kernels and the
+query to the finishing kernel.  Every output is compared with the CPU oracle,
+element by element.
+"""
+import numpy as np
+import pytest
+
+import kgsynth
+import paper_2110_14890_amd as sm
+from gpu_common import assert_same, gpu_sample, graph_pair, progress, require_gpu
+from test_gpu_parity import hub_graph_3p
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+# n_neg 550 is the longest row whose first draws are one window of 576, with
+# the selection table over the staged lists; 551 the shortest with its own
+@pytest.mark.parametrize("n_neg,neg_tries", [(1, 2), (56, 64), (57, 200), (549, 576), (550, 1000),
+                                             (551, 1000), (560, 4096), (1100, 1200), (4096, 4096)])
+def test_rows_around_the_window(n_neg, neg_tries):
+    rng = np.random.default_rng(21)
+    tr = kgsynth.random_tiny(rng, 6000, 4, 90000)
+    g, og = graph_pair(tr, 6000, 4, False)
+    for qt in ("1p", "3p", "ip", "pni"):
+        progress(f"window {qt} n_neg {n_neg}")
+        got = gpu_sample(g, qt, 65, n_neg, seed=2, neg_tries=neg_tries)
+        ref = og.sample(qt, 65, n_neg, seed=2, neg_tries=neg_tries)
+        assert_same(got, ref, what=f"{qt} n_neg {n_neg}")
+
+
+# 30 entities for up to 600 draws: nearly every draw repeats an earlier one,
+# within a step of 64, within a window and across windows
+@pytest.mark.parametrize("batch", [33, 4096])
+@pytest.mark.parametrize("qt", ["1p", "2p", "2u", "pin"])
+def test_repeated_draws(qt, batch):
+    rng = np.random.default_rng(22)
+    tr = kgsynth.random_tiny(rng, 30, 3, 150)
+    g, og = graph_pair(tr, 30, 3, False)
+    for n_neg, nt in [(20, 80), (29, 600)]:
+        got = gpu_sample(g, qt, batch, n_neg, seed=3, neg_tries=nt)
+        ref = og.sample(qt, batch, n_neg, seed=3, neg_tries=nt)
+        assert_same(got, ref, what=f"{qt} n_neg {n_neg}")
+
+
+# every backward list and forward list longer than a wavefront may walk:
+# queries deferred to the long-list kernels and finished after them
+@pytest.mark.parametrize("qt", ["2p", "3p", "ip", "pi", "up", "inp", "pin", "pni"])
+def test_long_lists_on_hub_graph(qt):
+    tr, V, R = hub_graph_3p()
+    # a second way into every y, so that two branches can meet there
+    extra = np.stack([np.full(400, 5), np.zeros(400, int), np.arange(2500, 2900)], 1)
+    tr = np.concatenate([tr, extra.astype(np.int32)])
+    g, og = graph_pair(tr, V, R)
+    for n_neg, nt in [(64, 300), (600, 2000)]:
+        progress(f"hub {qt} n_neg {n_neg}")
+        got = gpu_sample(g, qt, 150, n_neg, seed=4, neg_tries=nt)
+        ref = og.sample(qt, 150, n_neg, seed=4, neg_tries=nt)
+        assert_same(got, ref, what=f"hub {qt} n_neg {n_neg}")
