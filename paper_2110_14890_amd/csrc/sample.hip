@@ -1525,17 +1525,16 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
             to_stage = false;
         }
         // Every answer of every shape is reached by a projection, so a
-        // draw without an in-edge is a non-answer: the in-edge mask (V
-        // bits, resident in the last-level cache) decides most draws.
-        // On a large graph the coarse mask (one bit per four entities,
-        // small enough for the L2) is read first, and only draws whose
-        // group of four has an in-edge read their in-relation
-        // signature (a byte per entity), which must hold the bits of
-        // the relations that end at the root: a draw with in-edges
-        // only under other relation classes is a non-answer too.
+        // draw without an in-edge is a non-answer, and so is one whose
+        // in-relation signature (a byte per entity) lacks the classes of
+        // the relations that end at the root.  Which array is read first
+        // depends on what fits the L2 (g.first_test): the signatures
+        // themselves, or a mask of the entities with an in-edge (one bit
+        // per entity, or per four entities), after which only the draws it
+        // passes read their signature.
         int32_t c[DPW];
         uint32_t word[DPW];
-        const bool two_level = !use_lists && g.coarse;
+        const int test = use_lists ? -1 : g.first_test;
 #pragma unroll
         for (int k = 0; k < DPW; ++k) {
             const int32_t j = base + k * 64 + lane;
@@ -1543,8 +1542,11 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
             word[k] = 0;
             if (j < stop) {
                 c[k] = candidate(p, g.V, b, j);   // -1 (given candidates only): never a negative
-                if (!use_lists && c[k] >= 0)
-                    word[k] = two_level ? g.has_in4[c[k] >> 7] : g.has_in[c[k] >> 5];
+                if (c[k] >= 0) {
+                    if (test == TEST_SIG) word[k] = g.sig[c[k]];
+                    if (test == TEST_MASK) word[k] = g.has_in[c[k] >> 5] >> (c[k] & 31) & 1u;
+                    if (test == TEST_MASK4) word[k] = g.has_in4[c[k] >> 7] >> (c[k] >> 2 & 31) & 1u;
+                }
                 L.cand[k * 64 + lane] = c[k];
             }
         }
@@ -1552,16 +1554,14 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
             stage_lists();
             to_stage = false;
         }
-        if (two_level) {
+        if (!use_lists) {
 #pragma unroll
             for (int k = 0; k < DPW; ++k) {
-                // accounted as one mask line per draw, as the one-level test
-                const bool live = c[k] >= 0;
-                const bool maybe = live && ((word[k] >> ((c[k] >> 2) & 31)) & 1u);
-                if (live) tl.read(g.has_in4 + (c[k] >> 7), 4);
-                const uint32_t sg = maybe ? (uint32_t)g.sig[c[k]] : 0u;
-                const bool pass = RootRels<QT>::any ? (sg & need) != 0 : (sg & need) == need;
-                word[k] = pass ? ~0u : 0u;
+                // accounted as one line per draw, whichever array
+                if (c[k] >= 0) tl.read(g.has_in + (c[k] >> 5), 4);
+                uint32_t sg = word[k];
+                if (test != TEST_SIG) sg = word[k] ? (uint32_t)g.sig[c[k]] : 0u;
+                word[k] = (RootRels<QT>::any ? (sg & need) != 0 : (sg & need) == need) ? 1u : 0u;
             }
         }
         if (use_lists) {
@@ -1575,15 +1575,14 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
                     const bool h = maybe_in<QT>(L, f, c[k]);
                     hit = RootLists<QT>::any ? (hit || h) : (hit && h);
                 }
-                word[k] = hit ? ~0u : 0u;
+                word[k] = hit ? 1u : 0u;
             }
         }
         int32_t nsurv = 0;
 #pragma unroll
         for (int k = 0; k < DPW; ++k) {
             const bool live = c[k] >= 0;
-            const bool in = live && ((word[k] >> (c[k] & 31)) & 1u);
-            if (live && !use_lists && !two_level) tl.read(g.has_in + (c[k] >> 5), 4);
+            const bool in = live && word[k];
             const uint64_t ml = __ballot(live), m = __ballot(in);
             if (lane < 2) L.non[2 * k + lane] = (uint32_t)(ml >> (32 * lane));
             if (in) L.sj[nsurv + __popcll(m & below)] = (uint16_t)(k * 64 + lane);
@@ -2379,9 +2378,7 @@ GraphView view_of(const smore_graph* g)
     gv.has_in = g->has_in;
     gv.has_in4 = g->has_in4;
     gv.sig = g->sig;
-    // above 2 MiB of fine mask (V > 2^24) the coarse mask (a quarter of
-    // the size) answers most draws from the L2
-    gv.coarse = g->V > (1 << 24);
+    gv.first_test = g->V <= (1 << 22) ? TEST_SIG : g->V <= (1 << 24) ? TEST_MASK : TEST_MASK4;
     gv.V = g->V;
     gv.n_active = (int32_t)g->n_active;
     return gv;

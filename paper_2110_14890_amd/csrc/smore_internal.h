@@ -20,6 +20,12 @@ struct DirView {
     const int32_t* nbr;
 };
 
+// First test of a draw: the in-relation signatures while they fit an XCD's
+// L2 (4 MiB: V up to 2^22), else the in-edge mask while it does (V / 8 bytes,
+// V up to 2^24: half the L2), else the coarse mask; after a mask, the
+// signatures of the draws it passes.
+enum { TEST_SIG = 0, TEST_MASK = 1, TEST_MASK4 = 2 };
+
 struct GraphView {
     DirView fwd, rev;
     const int32_t* active_in;  // entities with an in-edge, ascending
@@ -27,7 +33,7 @@ struct GraphView {
     const uint32_t* has_in4;   // bit i: one of entities 4i .. 4i + 3 has an in-edge (V / 4 bits)
     const uint8_t* sig;        // in-relation signature of entity v: bit sig_bit(r) set for
                                // each relation r of its in-edges (V bytes, 0 without in-edge)
-    int32_t coarse;            // test has_in4, then sig (when has_in outgrows the L2)
+    int32_t first_test;        // which array the first test of a draw reads (TEST_*)
     int32_t V;
     int32_t n_active;
 };
