@@ -530,17 +530,21 @@ int run_sample(const smore_graph* g, const smore_query_dag* dag, const smore_sam
     if ((rc = check_graph_and_cut(g, dag, qt))) return rc;
     const smore::SampleParams p = params_of(a);
     const char* err = "";
+    if ((stages & NEG) && a->n_neg > 0 && (!workspace || ws_bytes < smore::negatives_workspace_bytes(p)))
+        return fail(SMORE_E_INVALID_ARG, "workspace missing or smaller than %zu bytes",
+                    smore::negatives_workspace_bytes(p));
     if (stages & POS) {
         smore::WalkProgram w;
         std::memset(&w, 0, sizeof(w));
         compile_walk(dag, dag->root, 0, &w);
-        rc = smore::launch_positive(g, w, p, *out, (hipStream_t)hip_stream, &err);
+        // a whole call with negatives to draw prepares them with the positives
+        const bool prepare = (stages & NEG) && a->n_neg > 0;
+        rc = smore::launch_positive(g, w, p, *out, qt, prepare ? workspace : nullptr,
+                                    (hipStream_t)hip_stream, &err);
         if (rc) return fail(rc, "positive sampling: %s", err);
+        if (prepare) parts &= ~smore::NEG_PREPARE;
     }
     if (stages & NEG) {
-        if (a->n_neg > 0 && (!workspace || ws_bytes < smore::negatives_workspace_bytes(p)))
-            return fail(SMORE_E_INVALID_ARG, "workspace missing or smaller than %zu bytes",
-                        smore::negatives_workspace_bytes(p));
         rc = smore::launch_negative(g, (smore::QType)qt, p, *out, stats, workspace, ws_bytes, parts,
                                     (hipStream_t)hip_stream, &err);
         if (rc) return fail(rc, "negative sampling: %s", err);
@@ -608,7 +612,10 @@ int smore_sample_shared(const smore_graph* g, const smore_query_dag* dag, const 
     std::memset(&w, 0, sizeof(w));
     compile_walk(dag, dag->root, 0, &w);
     const char* err = "";
-    rc = smore::launch_positive(g, w, p, pos, (hipStream_t)hip_stream, &err);
+    smore::SampleParams given = p;   // no per-query rows: a query without a positive writes none
+    given.shared_mode = 1;
+    rc = smore::launch_positive(g, w, given, pos, qt, a->n_neg > 0 ? workspace : nullptr,
+                                (hipStream_t)hip_stream, &err);
     if (rc) return fail(rc, "positive sampling: %s", err);
     rc = smore::launch_shared(g, (smore::QType)qt, p, pos, out->shared, out->n_shared, out->mask,
                               workspace, ws_bytes, (hipStream_t)hip_stream, &err);

@@ -501,49 +501,6 @@ __device__ __forceinline__ bool pos_attempt(const GraphView& g, const WalkProgra
     return true;
 }
 
-template <int PA>
-__global__ __launch_bounds__(256) void k_positive(GraphView g, WalkProgram wp, SampleParams p,
-                                                  smore_sample_out out)
-{
-    const int32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t b = gid / PA;
-    const int l = gid % PA;
-    if (b >= p.batch) return;   // whole groups: PA divides the workgroup size
-    const uint32_t q = (uint32_t)(p.query_offset + (uint64_t)b);
-    const int gbase = (threadIdx.x & 63) & ~(PA - 1);
-    int32_t e[5], qr[3];
-    int win = -1;
-    for (int t0 = 0; t0 < p.pos_tries; t0 += PA) {
-        const int t = t0 + l;
-        const bool ok = t < p.pos_tries && pos_attempt(g, wp, p, q, t, e, qr);
-        const uint32_t m = (uint32_t)(__ballot(ok) >> gbase) & ((1u << PA) - 1);
-        if (m) {
-            win = t0 + __ffs(m) - 1;
-            break;
-        }
-    }
-    if (win < 0) {
-        if (l == 0) {
-            int32_t* A = out.anchors + 3 * (int64_t)b;
-            int32_t* R = out.relations + 3 * (int64_t)b;
-            for (int k = 0; k < 3; ++k) { A[k] = -1; R[k] = -1; }
-            out.positive[b] = -1;
-            out.n_valid[b] = -1;
-            out.pos_attempts[b] = p.pos_tries;
-        }
-        return;
-    }
-    if (l != win % PA) return;  // the lane that ran the winning attempt writes the row
-    int32_t* A = out.anchors + 3 * (int64_t)b;
-    int32_t* R = out.relations + 3 * (int64_t)b;
-    for (int a = 0; a < 3; ++a) A[a] = a < wp.n_anchor ? reg5(wp.anchor_reg[a], e) : -1;
-    for (int sl = 0; sl < 3; ++sl) R[sl] = slot_rel(wp, qr, sl);
-    out.positive[b] = e[0];
-    out.n_valid[b] = 0;
-    out.pos_attempts[b] = win + 1;
-}
-
-
 // --------------------------------------------------------------- negatives
 // Bidirectional rejection sampling of the negatives, in rounds of candidate
 // draws.  Per round:
@@ -1190,7 +1147,107 @@ __device__ __forceinline__ bool query_ok(const GraphView& g, const smore_sample_
     return ok;
 }
 
-// Per query: validity, forward-cached lists, staging plan, active list.
+// Counters of a call: queued pairs, queries to finish, units.
+__device__ __forceinline__ void reset_counters(const Ws& ws)
+{
+    ws.ctrl[0] = 0;
+    ws.ctrl[2] = 0;
+    ws.ctrl[5] = 0;
+}
+
+// The preparation of the negatives as part of the positives' kernel: the
+// shape's lists (Shape), or nf = -1 for a call that only samples positives.
+struct PrepLists {
+    int32_t nf;
+    int32_t fa[3], fr[3];
+};
+
+// Preparation of a query whose lists' edge ranges r are held by its lanes
+// l = 0, 1, 2 (lane base + l of the wavefront): ranges, and the staging plan
+// in list order.
+__device__ __forceinline__ int32_t write_lists(int32_t* q, int2 r, int l, int base, int nf)
+{
+    if (l < nf) {
+        q[2 * l] = r.x;
+        q[2 * l + 1] = r.y;
+    }
+    int32_t used = 0, staged = 0;
+    for (int k = 0; k < nf; ++k) {
+        const int32_t n = __shfl(r.y - r.x, base + k);
+        if (n <= STAGE - used) {
+            staged |= 1 << k;
+            used += n;
+        }
+    }
+    if (l == 0) q[6] = staged;
+    return staged;
+}
+
+// With a preparation to do, the lanes of a query share its winning row and
+// look its lists up, lane l list l (the plan has at most PA): the chain of
+// reads of k_prepare without its launch, which was 5 to 8 us of a call.
+template <int PA>
+__global__ __launch_bounds__(256) void k_positive(GraphView g, WalkProgram wp, SampleParams p,
+                                                  smore_sample_out out, PrepLists lists, Ws ws)
+{
+    const int32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t b = gid / PA;
+    const int l = gid % PA;
+    if (b >= p.batch) return;   // whole groups: PA divides the workgroup size
+    const bool prepare = lists.nf >= 0;
+    if (prepare && gid == 0) reset_counters(ws);
+    const uint32_t q = (uint32_t)(p.query_offset + (uint64_t)b);
+    const int gbase = (threadIdx.x & 63) & ~(PA - 1);
+    int32_t e[5], qr[3];
+    int win = -1;
+    for (int t0 = 0; t0 < p.pos_tries; t0 += PA) {
+        const int t = t0 + l;
+        const bool ok = t < p.pos_tries && pos_attempt(g, wp, p, q, t, e, qr);
+        const uint64_t m = (__ballot(ok) >> gbase) & (~0ull >> (64 - PA));
+        if (m) {
+            win = t0 + __ffsll((unsigned long long)m) - 1;
+            break;
+        }
+    }
+    int32_t A[3], R[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        A[k] = win >= 0 && k < wp.n_anchor ? reg5(wp.anchor_reg[k], e) : -1;
+        R[k] = win >= 0 ? slot_rel(wp, qr, k) : -1;
+    }
+    if (l == (win < 0 ? 0 : win % PA)) {   // the lane that ran the winning attempt writes the row
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            out.anchors[3 * (int64_t)b + k] = A[k];
+            out.relations[3 * (int64_t)b + k] = R[k];
+        }
+        out.positive[b] = win < 0 ? -1 : e[0];
+        out.n_valid[b] = win < 0 ? -1 : 0;
+        out.pos_attempts[b] = win < 0 ? p.pos_tries : win + 1;
+    }
+    if (!prepare) return;
+    int32_t* qf = ws.qf + (int64_t)b * QF;
+    if (win < 0) {
+        if (l == 0) {
+            write_undrawn_row(p, out, b, false);
+            qf[6] = -1;   // skipped by the candidate kernel
+        }
+        return;
+    }
+    const int from = gbase + win % PA;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        A[k] = __shfl(A[k], from);
+        R[k] = __shfl(R[k], from);
+    }
+    int2 r = make_int2(0, 0);
+    if (l < lists.nf)
+        r = group_range(g.fwd, sel4(lists.fa[l], A[0], A[1], A[2], -1), sel4(lists.fr[l], R[0], R[1], R[2], -1));
+    write_lists(qf, r, l, gbase, lists.nf);
+}
+
+// Per query: validity, forward-cached lists, staging plan, for queries that
+// the same call does not sample.
 // Four neighbouring lanes per query: lane f looks up list f, so the
 // dependent lookups of a query's lists run side by side; the staging plan
 // is made from the sizes of all its lists, in list order.
@@ -1202,11 +1259,7 @@ __global__ __launch_bounds__(256) void k_prepare(GraphView g, SampleParams p, sm
     const int32_t b = gid >> 2;
     const int f = gid & 3;
     if (b >= p.batch) return;   // whole groups: 4 divides the workgroup size
-    if (gid == 0) {   // counters: queued pairs, queries to finish, units
-        ws.ctrl[0] = 0;
-        ws.ctrl[2] = 0;
-        ws.ctrl[5] = 0;
-    }
+    if (gid == 0) reset_counters(ws);
     int32_t anc[3], rel[3];
     int32_t* q = ws.qf + (int64_t)b * QF;
     if (f == 0 && stats)
@@ -1220,22 +1273,10 @@ __global__ __launch_bounds__(256) void k_prepare(GraphView g, SampleParams p, sm
     }
     T tl;
     int2 r = make_int2(0, 0);
-    if (f < Shape<QT>::nf) {
-        r = group_range(g.fwd, anc[Shape<QT>::fa[f]], rel[Shape<QT>::fr[f]], tl);
-        q[2 * f] = r.x;
-        q[2 * f + 1] = r.y;
-    }
+    if (f < Shape<QT>::nf) r = group_range(g.fwd, anc[Shape<QT>::fa[f]], rel[Shape<QT>::fr[f]], tl);
     const int base = (threadIdx.x & 63) & ~3;
-    int32_t used = 0, staged = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int32_t n = __shfl(r.y - r.x, base + k);
-        if (k < Shape<QT>::nf && n <= STAGE - used) {
-            staged |= 1 << k;
-            used += n;
-        }
-    }
-    if (f == 0) q[6] = staged;
+    const int32_t staged = write_lists(q, r, f, base, Shape<QT>::nf);
+    (void)staged;
     if constexpr (T::on) {
         // forward caching reads the list once; a staged anchor list too
         if (f < Shape<QT>::nf && (Shape<QT>::cached[f] || (staged >> f & 1)))
@@ -2331,15 +2372,17 @@ int draw_shared_set(const SampleParams& p, int32_t V, int32_t* shared, int32_t* 
 // list per query p.cand_stride apart): states, then mask rows and counts.
 template <int QT>
 int run_pairs(const GraphView& gv, const SampleParams& p, const smore_sample_out& q, Ws ws,
-              uint32_t* mask, int32_t R, hipStream_t st, const char** err)
+              uint32_t* mask, int32_t R, bool prepared, hipStream_t st, const char** err)
 {
     int rc;
     if (p.n_neg == 0) {   // no candidates: n_valid only (0, or -1 for a skipped query)
         k_no_draws<QT><<<(p.batch + 255) / 256, 256, 0, st>>>(gv, p, q, nullptr, R);
         return check_launch(err);
     }
-    k_prepare<QT, NoTally><<<(p.batch + 63) / 64, 256, 0, st>>>(gv, p, q, ws, nullptr, R);
-    if ((rc = check_launch(err))) return rc;
+    if (!prepared) {
+        k_prepare<QT, NoTally><<<(p.batch + 63) / 64, 256, 0, st>>>(gv, p, q, ws, nullptr, R);
+        if ((rc = check_launch(err))) return rc;
+    }
     k_pairs<QT><<<p.batch, CWG, 0, st>>>(gv, p, q, ws, mask);
     if ((rc = check_launch(err))) return rc;
     if constexpr (has_long_lists<QT>)
@@ -2348,24 +2391,55 @@ int run_pairs(const GraphView& gv, const SampleParams& p, const smore_sample_out
 }
 
 int dispatch_pairs(QType qt, const GraphView& gv, const SampleParams& p, const smore_sample_out& q,
-                   Ws ws, uint32_t* mask, int32_t R, hipStream_t st, const char** err)
+                   Ws ws, uint32_t* mask, int32_t R, bool prepared, hipStream_t st, const char** err)
 {
     switch (qt) {
-        case Q1P: return run_pairs<Q1P>(gv, p, q, ws, mask, R, st, err);
-        case Q2P: return run_pairs<Q2P>(gv, p, q, ws, mask, R, st, err);
-        case Q3P: return run_pairs<Q3P>(gv, p, q, ws, mask, R, st, err);
-        case Q2I: return run_pairs<Q2I>(gv, p, q, ws, mask, R, st, err);
-        case Q3I: return run_pairs<Q3I>(gv, p, q, ws, mask, R, st, err);
-        case QIP: return run_pairs<QIP>(gv, p, q, ws, mask, R, st, err);
-        case QPI: return run_pairs<QPI>(gv, p, q, ws, mask, R, st, err);
-        case Q2U: return run_pairs<Q2U>(gv, p, q, ws, mask, R, st, err);
-        case QUP: return run_pairs<QUP>(gv, p, q, ws, mask, R, st, err);
-        case Q2IN: return run_pairs<Q2IN>(gv, p, q, ws, mask, R, st, err);
-        case Q3IN: return run_pairs<Q3IN>(gv, p, q, ws, mask, R, st, err);
-        case QINP: return run_pairs<QINP>(gv, p, q, ws, mask, R, st, err);
-        case QPIN: return run_pairs<QPIN>(gv, p, q, ws, mask, R, st, err);
-        case QPNI: return run_pairs<QPNI>(gv, p, q, ws, mask, R, st, err);
+        case Q1P: return run_pairs<Q1P>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q2P: return run_pairs<Q2P>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q3P: return run_pairs<Q3P>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q2I: return run_pairs<Q2I>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q3I: return run_pairs<Q3I>(gv, p, q, ws, mask, R, prepared, st, err);
+        case QIP: return run_pairs<QIP>(gv, p, q, ws, mask, R, prepared, st, err);
+        case QPI: return run_pairs<QPI>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q2U: return run_pairs<Q2U>(gv, p, q, ws, mask, R, prepared, st, err);
+        case QUP: return run_pairs<QUP>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q2IN: return run_pairs<Q2IN>(gv, p, q, ws, mask, R, prepared, st, err);
+        case Q3IN: return run_pairs<Q3IN>(gv, p, q, ws, mask, R, prepared, st, err);
+        case QINP: return run_pairs<QINP>(gv, p, q, ws, mask, R, prepared, st, err);
+        case QPIN: return run_pairs<QPIN>(gv, p, q, ws, mask, R, prepared, st, err);
+        case QPNI: return run_pairs<QPNI>(gv, p, q, ws, mask, R, prepared, st, err);
         default: *err = "unknown shape"; return SMORE_E_UNSUPPORTED;
+    }
+}
+
+template <int QT> PrepLists lists_of()
+{
+    PrepLists l{};
+    l.nf = Shape<QT>::nf;
+    for (int f = 0; f < 3; ++f) {
+        l.fa[f] = Shape<QT>::fa[f];
+        l.fr[f] = Shape<QT>::fr[f];
+    }
+    return l;
+}
+
+PrepLists prep_lists(QType qt)
+{
+    switch (qt) {
+        case Q1P: return lists_of<Q1P>();
+        case Q2P: return lists_of<Q2P>();
+        case Q3P: return lists_of<Q3P>();
+        case Q2I: return lists_of<Q2I>();
+        case Q3I: return lists_of<Q3I>();
+        case QIP: return lists_of<QIP>();
+        case QPI: return lists_of<QPI>();
+        case Q2U: return lists_of<Q2U>();
+        case QUP: return lists_of<QUP>();
+        case Q2IN: return lists_of<Q2IN>();
+        case Q3IN: return lists_of<Q3IN>();
+        case QINP: return lists_of<QINP>();
+        case QPIN: return lists_of<QPIN>();
+        default: return lists_of<QPNI>();
     }
 }
 
@@ -2439,24 +2513,49 @@ size_t negatives_workspace_bytes(const SampleParams& p)
     return ws_layout(p, nullptr, nullptr);
 }
 
-int launch_positive(const smore_graph* g, const WalkProgram& wp, const SampleParams& p,
-                    const smore_sample_out& out, hipStream_t st, const char** err)
+// Attempt lanes per query (they divide 64).  Attempts past the first
+// successful one are wasted reads, so plans that usually succeed at once run
+// two.  Plans accept less often per attempt when sibling branches hang off
+// the root (two of them must not draw the same in-relation and in-neighbour
+// of the root, which seldom has many) or with a complemented operand: four
+// lanes, eight with three root siblings; and a maximum expansion C rejects
+// every attempt through a wider step: eight lanes.  Such plans get more as
+// long as the call stays within one wavefront per SIMD (65,536 lanes), where
+// the reads cost nothing and the kernel's time is that of its unluckiest
+// query: with 64 lanes in place of 8 and the preparation in the same kernel, a
+// 2p call of 1,024 queries at C = 10 (Freebase-shaped, 34 attempts on average)
+// went from 137 to 67 us; with 8 in place of 4, 2i x 8,192 from 56 to 49.
+inline int positive_lanes(const WalkProgram& wp, const SampleParams& p)
 {
-    // attempt lanes per query (they divide 64): attempts past the first
-    // successful one are wasted reads, so plans that usually succeed at once
-    // run two.  Plans accept less often per attempt when sibling branches
-    // hang off the root (two of them must not draw the same in-relation and
-    // in-neighbour of the root, which seldom has many) or with a
-    // complemented operand: four lanes, eight with three root siblings; and
-    // a maximum expansion C rejects every attempt through a wider step:
-    // eight lanes.
-    const int pa = (wp.root_pairs >= 3 || p.max_fanout > 0) ? 8
-                   : (wp.root_pairs > 0 || wp.neg_steps > 0) ? 4 : 2;
-    const int64_t threads = (int64_t)p.batch * pa;
-    const unsigned blocks = (unsigned)((threads + 255) / 256);
-    if (pa == 8) k_positive<8><<<blocks, 256, 0, st>>>(view_of(g), wp, p, out);
-    else if (pa == 4) k_positive<4><<<blocks, 256, 0, st>>>(view_of(g), wp, p, out);
-    else k_positive<2><<<blocks, 256, 0, st>>>(view_of(g), wp, p, out);
+    const bool capped = p.max_fanout > 0;
+    int pa = (wp.root_pairs >= 3 || capped) ? 8 : (wp.root_pairs > 0 || wp.neg_steps > 0) ? 4 : 2;
+    const int most = capped ? 64 : pa > 2 ? 16 : 2;
+    while (pa < most && (int64_t)p.batch * pa * 2 <= 65536) pa *= 2;
+    return pa;
+}
+
+int launch_positive(const smore_graph* g, const WalkProgram& wp, const SampleParams& p,
+                    const smore_sample_out& out, int qt, void* workspace, hipStream_t st,
+                    const char** err)
+{
+    Ws ws{};
+    PrepLists lists{};
+    lists.nf = -1;
+    if (workspace) {
+        ws_layout(p, &ws, (char*)workspace);
+        lists = prep_lists((QType)qt);
+    }
+    const int pa = positive_lanes(wp, p);
+    const unsigned blocks = (unsigned)(((int64_t)p.batch * pa + 255) / 256);
+    auto run = [&](auto kernel) { kernel<<<blocks, 256, 0, st>>>(view_of(g), wp, p, out, lists, ws); };
+    switch (pa) {
+        case 2: run(k_positive<2>); break;
+        case 4: run(k_positive<4>); break;
+        case 8: run(k_positive<8>); break;
+        case 16: run(k_positive<16>); break;
+        case 32: run(k_positive<32>); break;
+        default: run(k_positive<64>); break;
+    }
     return check_launch(err);
 }
 
@@ -2495,7 +2594,7 @@ int launch_shared(const smore_graph* g, QType qt, const SampleParams& p0, const 
     // an empty set leaves nothing to verify: the positives' n_valid (0, or -1
     // without a positive) is the row count, and no mask word exists
     if (rc || p.n_neg == 0) return rc;
-    return dispatch_pairs(qt, gv, p, pos, ws, mask, g->R, st, err);
+    return dispatch_pairs(qt, gv, p, pos, ws, mask, g->R, true, st, err);
 }
 
 int launch_verify(const smore_graph* g, QType qt, const SampleParams& p0, const int32_t* anchors,
@@ -2519,7 +2618,7 @@ int launch_verify(const smore_graph* g, QType qt, const SampleParams& p0, const 
     q.anchors = (int32_t*)anchors;
     q.relations = (int32_t*)relations;
     q.n_valid = n_valid;
-    return dispatch_pairs(qt, view_of(g), p, q, ws, mask, g->R, st, err);
+    return dispatch_pairs(qt, view_of(g), p, q, ws, mask, g->R, false, st, err);
 }
 
 }  // namespace smore

@@ -112,14 +112,17 @@ struct smore_graph {
 namespace smore {
 int build_graph_device(const int32_t* triples_host, int64_t n, int32_t V, int32_t R,
                        bool add_inverse, smore_graph* g, const char** err);
+// with a workspace, the preparation of the negatives (NEG_PREPARE) too
 int launch_positive(const smore_graph* g, const WalkProgram& wp, const SampleParams& p,
-                    const smore_sample_out& out, hipStream_t stream, const char** err);
+                    const smore_sample_out& out, int qt, void* workspace, hipStream_t stream,
+                    const char** err);
 // Parts of the negative stage (bit masks for launch_negative).
 constexpr int NEG_PREPARE = 1, NEG_CANDIDATES = 2, NEG_REST = 4, NEG_ALL = 7;
 int launch_negative(const smore_graph* g, QType qt, const SampleParams& p,
                     const smore_sample_out& out, int64_t* stats, void* workspace, size_t ws_bytes,
                     int parts, hipStream_t stream, const char** err);
 size_t negatives_workspace_bytes(const SampleParams& p);
+// the queries are prepared (launch_positive with the workspace)
 int launch_shared(const smore_graph* g, QType qt, const SampleParams& p, const smore_sample_out& pos,
                   int32_t* shared, int32_t* n_shared, uint32_t* mask, void* workspace,
                   size_t ws_bytes, hipStream_t stream, const char** err);

@@ -64,3 +64,18 @@ def test_long_lists_on_hub_graph(qt):
         got = gpu_sample(g, qt, 150, n_neg, seed=4, neg_tries=nt)
         ref = og.sample(qt, 150, n_neg, seed=4, neg_tries=nt)
         assert_same(got, ref, what=f"hub {qt} n_neg {n_neg}")
+
+
+# attempt lanes per query: 64 and 32 under a maximum expansion, 16, 8 and 4
+# for plans with root siblings or a complemented operand; attempt budgets
+# that are no multiple of the lanes
+@pytest.mark.parametrize("qt,batch,max_fanout", [("2p", 7, 3), ("ip", 1025, 3), ("pni", 2049, 5), ("3i", 70, 0),
+                                                 ("3in", 4097, 0), ("2u", 9000, 0), ("up", 300, 2)])
+def test_attempt_lanes(qt, batch, max_fanout):
+    rng = np.random.default_rng(23)
+    tr = kgsynth.random_tiny(rng, 2000, 5, 12000)
+    g, og = graph_pair(tr, 2000, 5, False)
+    for pos_tries in (1, 5, 64, 67):
+        got = gpu_sample(g, qt, batch, 4, seed=6, pos_tries=pos_tries, max_fanout=max_fanout)
+        ref = og.sample(qt, batch, 4, seed=6, pos_tries=pos_tries, max_fanout=max_fanout)
+        assert_same(got, ref, what=f"{qt} batch {batch} pos_tries {pos_tries}")
