@@ -599,7 +599,7 @@ constexpr int CWG = 64;
 constexpr int HEAVY_WG = 256;    // threads of the heavy-queue workgroups
 constexpr int QF = 8;            // int32 per query in the per-query block
 constexpr int PERSIST_BLOCKS = 2048;
-constexpr int FINISH_BLOCKS = 4096;   // one-wave workgroups of the finishing kernel
+constexpr int FINISH_BLOCKS = 1024;   // workgroups of the finishing kernel
 // 3p long-list work in bounded units: the long-list kernel expands at most
 // UNIT_Y entities y of an item and searches at most UNIT_PAIRS pairs of one
 // y itself; the rest become units of the unit queue (UNITS_PER_QUERY slots
@@ -933,28 +933,34 @@ __device__ __forceinline__ int32_t excl_prefix(int32_t v, int lane, int32_t* tot
 // The deep pass over up to 64 candidates, one per lane: lane l's candidate
 // has the backward list [start, start + len) (len 0: none).  Returns the
 // lanes whose chain meets the cached lists, and in *pend those left to a
-// whole wavefront.  The entries y of all lists are laid out over the lanes,
-// 64 per step; for 3p so are the (y, key) pairs of each 64 y's, keys from the
-// shorter of R_r1(y) and F0.  So the dependent reads of the pass are those
-// of its deepest candidate, not the sum over a lane's entries (one lane
-// walking its own list: 172 + 77 us in two rounds for 512 3p queries x 128
-// on an FB15k-237-shaped graph; laid out: 67 us for all draws).  A list over DEEP_LONG
-// entries, or past DEEP_TOTAL entries of the pass, is left, and so is
-// everything once the query has taken DEEP_STEPS steps (`steps` counts them
-// down): a wavefront of its own (or, for 3p, several) shortens the longest
-// wavefront of the call.
-constexpr int DEEP_LONG = 512, DEEP_TOTAL = 4096, DEEP_STEPS = 48;
+// whole wavefront.  All (entry, list) pairs to test are laid out over the
+// lanes, with keys from the shorter of the backward list and the cached one
+// (for 3p the entries y of all lists 64 at a time, and of each 64 the pairs
+// of R_r1(y) and F0), so the dependent reads of the pass are those of its
+// deepest candidate, not the sum over a lane's entries (one lane walking its
+// own list: 172 + 77 us in two rounds for 512 3p queries x 128 on an
+// FB15k-237-shaped graph; laid out: 67 us for all draws).  A candidate with
+// over DEEP_LONG pairs, or past DEEP_TOTAL pairs of the pass, is left, and
+// so is everything once the query has taken DEEP_STEPS steps (`steps` counts
+// them down): a wavefront of its own (or, for 3p, several) shortens the
+// longest wavefront of the call.  48 steps: 3p x 1,000 negatives on an
+// FB400k-shaped graph 360 us a call, the FB15k-237-shaped step 385; 12: 301
+// and 379; 4: 312 and 508.  Two pairs per lane and step pay for the short
+// chains of the other shapes (FB400k-shaped 2p 87 -> 69 us with the keys
+// from the shorter list), not for 3p (Freebase-shaped step 618 against 604).
+constexpr int DEEP_LONG = 512, DEEP_TOTAL = 4096, DEEP_STEPS = 12;
+constexpr int DEEP_LEN = 65535;   // lengths are kept in 16 bits; one that long is left
 
-// Drops from len the lists the pass leaves; returns the lanes dropped.
-__device__ __forceinline__ uint64_t deep_limit(int32_t& len, int lane)
+// Drops from np the candidates the pass leaves; returns the lanes dropped.
+__device__ __forceinline__ uint64_t deep_limit(int32_t& np, int lane)
 {
-    bool over = len > DEEP_LONG;
-    if (over) len = 0;
+    bool over = np > DEEP_LONG;
+    if (over) np = 0;
     int32_t tot;
-    const int32_t ex = excl_prefix(len, lane, &tot);
+    const int32_t ex = excl_prefix(np, lane, &tot);
     if (tot > DEEP_TOTAL) {
-        over = over || (len > 0 && ex + len > DEEP_TOTAL);
-        if (over) len = 0;
+        over = over || (np > 0 && ex + np > DEEP_TOTAL);
+        if (over) np = 0;
     }
     return __ballot(over);
 }
@@ -970,41 +976,88 @@ __device__ __forceinline__ uint64_t owners_of(bool hit, int owner)
     return res;
 }
 
+// Entry k of list f.
+__device__ __forceinline__ int32_t list_entry(const GraphView& g, const WaveLds& L, const FList& F, int32_t k)
+{
+    return F.lds ? L.stage[F.off + k] : g.fwd.nbr[F.beg + k];
+}
+
 template <int QT, class T>
 __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds& L, const FList* F,
                                               const int32_t* rel, int32_t start, int32_t len, int lane,
                                               int32_t& steps, uint64_t* pend, T& tl)
 {
-    uint64_t left = deep_limit(len, lane), ans = 0;
-    int32_t total;
-    const int32_t ex = excl_prefix(len, lane, &total);
-    const uint32_t b1 = sig_bit(rel[1]);
-    for (int32_t y0 = 0; y0 < total; y0 += 64) {
-        if (--steps < 0) {   // the lists that reach past entry y0
-            left |= __ballot(len > 0 && ex + len > y0);
-            break;
-        }
-        const bool on = y0 + lane < total;
-        const int it = owner_lane(min(y0 + lane, total - 1), ex);
-        const int32_t at = __shfl(start, it) + y0 + lane - __shfl(ex, it);
-        int32_t y = -1;
-        if (on) {
-            y = g.rev.nbr[at];
-            tl.read(g.rev.nbr + at, 4);
-        }
-        if constexpr (QT != Q3P) {
-            bool hit = false;
-            if (on) {
-                hit = in_list<QT>(g, L, F, 0, y);
-                if (QT == QIP) hit = hit && in_list<QT>(g, L, F, 1, y);
-                if (QT == QINP) hit = hit && !in_list<QT>(g, L, F, 1, y);
-                if (QT == QUP) hit = hit || in_list<QT>(g, L, F, 1, y);
+    uint64_t left = 0, ans = 0;
+    if constexpr (QT != Q3P) {
+        // keys of a list longer than the cached ones: their entries (both
+        // for a union of chains)
+        const int32_t nf = QT == QUP ? F[0].n + F[1].n : F[0].n;
+        int32_t np = len >= DEEP_LEN ? INT_MAX : min(len, nf);
+        left = deep_limit(np, lane);
+        int32_t total;
+        const int32_t ex = excl_prefix(np, lane, &total);
+        for (int32_t p0 = 0; p0 < total; p0 += 128) {
+            if (--steps < 0) {   // the candidates that reach past pair p0
+                left |= __ballot(np > 0 && ex + np > p0);
+                break;
             }
-            ans |= owners_of(hit, it);
-        } else {
-            // y without an in-edge under r1's signature class has none under r1
+            bool on[2], hit[2];
+            int it[2];
+            int32_t off[2], st[2], ln[2], y[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int32_t pi = p0 + 64 * u + lane;
+                on[u] = pi < total;
+                it[u] = owner_lane(min(pi, total - 1), ex);
+                off[u] = pi - __shfl(ex, it[u]);
+                st[u] = __shfl(start, it[u]);
+                ln[u] = __shfl(len, it[u]);
+                hit[u] = false;
+                y[u] = -1;
+                if (on[u]) {
+                    if (ln[u] <= nf) {
+                        y[u] = g.rev.nbr[st[u] + off[u]];
+                        tl.read(g.rev.nbr + st[u] + off[u], 4);
+                    } else if (QT == QUP && off[u] >= F[0].n) {
+                        y[u] = list_entry(g, L, F[1], off[u] - F[0].n);
+                    } else {
+                        y[u] = list_entry(g, L, F[0], off[u]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (!on[u]) continue;
+                if (ln[u] <= nf) {
+                    hit[u] = in_list<QT>(g, L, F, 0, y[u]);
+                    if (QT == QUP) hit[u] = hit[u] || in_list<QT>(g, L, F, 1, y[u]);
+                } else {
+                    hit[u] = has8(g.rev.nbr + st[u], ln[u], y[u], true, tl);
+                }
+                if (QT == QIP) hit[u] = hit[u] && in_list<QT>(g, L, F, 1, y[u]);
+                if (QT == QINP) hit[u] = hit[u] && !in_list<QT>(g, L, F, 1, y[u]);
+            }
+            ans |= owners_of(hit[0], it[0]) | owners_of(hit[1], it[1]);
+        }
+    } else {
+        left = deep_limit(len, lane);
+        int32_t total;
+        const int32_t ex = excl_prefix(len, lane, &total);
+        const uint32_t b1 = sig_bit(rel[1]);
+        const int32_t nf = F[0].n;
+        for (int32_t y0 = 0; y0 < total; y0 += 64) {
+            if (--steps < 0) {
+                left |= __ballot(len > 0 && ex + len > y0);
+                break;
+            }
+            const bool on = y0 + lane < total;
+            const int it = owner_lane(min(y0 + lane, total - 1), ex);
+            const int32_t at = __shfl(start, it) + y0 + lane - __shfl(ex, it);
             int2 s2 = make_int2(0, 0);
             if (on && !((ans | left) >> it & 1)) {
+                // y without an in-edge under r1's signature class has none under r1
+                const int32_t y = g.rev.nbr[at];
+                tl.read(g.rev.nbr + at, 4);
                 tl.read(g.sig + y, 1);
                 const int32_t a0 = g.rev.node[y], a1 = g.rev.node[y + 1];
                 if (g.sig[y] & b1) {
@@ -1012,9 +1065,8 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
                     s2 = group_find(g.rev, a0, a1, rel[1], tl);
                 }
             }
-            const int32_t n2 = s2.y - s2.x, nf = F[0].n;
+            const int32_t n2 = s2.y - s2.x;
             int32_t np = min(n2, nf);
-            left |= owners_of(np > DEEP_LONG, it);
             const uint64_t over = deep_limit(np, lane);
             if (over) left |= owners_of(over >> lane & 1, it);
             int32_t ptotal;
@@ -1024,18 +1076,18 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
                     left |= owners_of(np > 0 && pex + np > p0, it);
                     break;
                 }
-                const int yl = owner_lane(min(p0 + lane, ptotal - 1), pex);
-                const int32_t off = p0 + lane - __shfl(pex, yl);
+                const int32_t pi = p0 + lane;
+                const int yl = owner_lane(min(pi, ptotal - 1), pex);
+                const int32_t off = pi - __shfl(pex, yl);
                 const int32_t lx = __shfl(s2.x, yl), ln = __shfl(n2, yl);
                 const int who = __shfl(it, yl);
                 bool hit = false;
-                if (p0 + lane < ptotal && !((ans | left) >> who & 1)) {
+                if (pi < ptotal && !((ans | left) >> who & 1)) {
                     if (ln <= nf) {
                         tl.read(g.rev.nbr + lx + off, 4);
                         hit = in_list<QT>(g, L, F, 0, g.rev.nbr[lx + off]);
                     } else {
-                        const int32_t x = F[0].lds ? L.stage[F[0].off + off] : g.fwd.nbr[F[0].beg + off];
-                        hit = has8(g.rev.nbr + lx, ln, x, true, tl);
+                        hit = has8(g.rev.nbr + lx, ln, list_entry(g, L, F[0], off), true, tl);
                     }
                 }
                 ans |= owners_of(hit, who);
@@ -1638,7 +1690,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
             if (st == ST_PEND) {
                 left = true;
                 if constexpr (MODE != DRAW_GIVEN) L.cand[i] = ~L.cand[i];
-                if constexpr (MODE != DRAW_FINISH) {
+                if constexpr (MODE == DRAW_GIVEN || (MODE == DRAW_FIRST && QT == Q3P)) {
                     const int32_t slot = atomicAdd(&ws.ctrl[0], 1);   // capacity covers a round
                     ws.queue[slot] = make_int2(b, base + i);
                 }
@@ -1796,20 +1848,57 @@ __global__ __launch_bounds__(CWG, 4) void k_pairs(GraphView g, SampleParams p, s
                                          blockIdx.x, n, threadIdx.x);
 }
 
-// The queries that had long lists among their first draws, once those are
-// settled: selection, and whatever further draws they need.  Persistent
-// one-wave workgroups over the list.
+// The queries that had long lists among their first draws: their verdicts
+// (for 3p the long-list kernels have settled them), selection, and whatever
+// further draws the queries need.  Persistent workgroups of four wavefronts
+// over the list: the long lists of a query are dealt over the four, the rest
+// is the first one's.  (A kernel of its own for the long lists was a launch
+// of 4 to 16 us for a few queries.)
+constexpr int FINISH_WG = 256;
 template <int QT, class T>
-__global__ __launch_bounds__(CWG, 4) void k_finish(GraphView g, SampleParams p, smore_sample_out out, Ws ws,
-                                                int64_t* stats, Table tb)
+__global__ __launch_bounds__(FINISH_WG, 4) void k_finish(GraphView g, SampleParams p, smore_sample_out out,
+                                                         Ws ws, int64_t* stats, Table tb)
 {
     __shared__ WaveLds L;
     extern __shared__ __align__(16) int32_t own_tab[];
+    const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
     const int32_t n = uni(ws.ctrl[2]);
     for (int32_t qi = blockIdx.x; qi < n; qi += gridDim.x) {
-        query_draws<QT, T, DRAW_FINISH>(g, p, out, ws, stats, nullptr, tb, own_tab, L,
-                                        uni(ws.act[0][qi]), 0, threadIdx.x);
-        wave_sync();
+        const int32_t b = uni(ws.act[0][qi]);
+        if constexpr (QT != Q3P) {
+            const int32_t* qb = ws.qf + (int64_t)b * QF;
+            const int32_t j0 = range_lo(uni(qb[7])), j1 = range_hi(uni(qb[7]));
+            uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
+            int32_t rel[3];
+            FSet F[3];
+            T tl;
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {
+                rel[f] = uni(out.relations[3 * (int64_t)b + f]);
+                F[f] = FSet{nullptr, 0};
+                if (f < Shape<QT>::nf) {
+                    const int32_t beg = uni(qb[2 * f]);
+                    F[f] = FSet{g.fwd.nbr + beg, uni(qb[2 * f + 1]) - beg};
+                }
+            }
+            for (int32_t k0 = j0; k0 < j1; k0 += 64) {
+                // every fourth draw: no wavefront reads a state that another one writes
+                const bool mine = (lane & 3) == w && k0 + lane < j1 && sv[k0 + lane] == ST_PEND;
+                for (uint64_t m = __ballot(mine); m; m &= m - 1) {
+                    const int32_t j = k0 + __ffsll((unsigned long long)m) - 1;
+                    const int2 s = group_range(g.rev, candidate(p, g.V, b, j), chain_r1<QT> ? rel[1] : rel[2], tl);
+                    if constexpr (T::on)
+                        if (lane != 0) tl = T();   // the wave's lookup, charged once
+                    const bool ans = heavy_test<QT>(g, F, rel, make_int2(uni(s.x), uni(s.y)), lane, tl);
+                    if (lane == 0) sv[j] = ans ? ST_ANS : ST_NON;
+                }
+            }
+            flush_tally(tl, stats, b, lane, 2);
+            __syncthreads();
+        }
+        if (w == 0)
+            query_draws<QT, T, DRAW_FINISH>(g, p, out, ws, stats, nullptr, tb, own_tab, L, b, 0, lane);
+        __syncthreads();
     }
 }
 
@@ -2263,14 +2352,15 @@ int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample
     }
     if (!(parts & NEG_REST)) return SMORE_OK;
     prof_mark(1, false, st);
-    if constexpr (has_long_lists<QT>) {
+    if constexpr (QT == Q3P) {
         if ((rc = launch_long_lists<QT, T>(gv, p, out, ws, stats, nullptr, st, err))) return rc;
     }
     prof_mark(1, true, st);
     prof_mark(2, false, st);
     if constexpr (has_long_lists<QT>) {
-        k_finish<QT, T><<<p.batch < FINISH_BLOCKS ? p.batch : FINISH_BLOCKS, CWG, own, st>>>(gv, p, out, ws,
-                                                                                            stats, tb);
+        // (3p leaves it no long lists: one-wave workgroups, four times as many)
+        const int wg = QT == Q3P ? 64 : FINISH_WG;
+        k_finish<QT, T><<<min(p.batch, FINISH_BLOCKS * FINISH_WG / wg), wg, own, st>>>(gv, p, out, ws, stats, tb);
         if ((rc = check_launch(err))) return rc;
     }
     prof_mark(2, true, st);
