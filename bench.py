@@ -63,10 +63,14 @@ def sample_hip_sha():
         return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
-def first_round_draws(n_neg, neg_tries):
+def first_round_draws(n_neg, neg_tries, batch=4096):
     """Candidate draws of the first round of smore_sample_negatives: n_neg
-    plus a margin of n_neg / 32 + 8, at most neg_tries."""
-    return min(n_neg + n_neg // 32 + 8, neg_tries)
+    plus a margin of n_neg / 32 + 8, at most neg_tries; a batch under 4,096
+    fills its last 64 draws up."""
+    e = min(n_neg + n_neg // 32 + 8, neg_tries)
+    if batch >= 4096:
+        return e
+    return max(e, min((e + 16 + 63) // 64 * 64, neg_tries, max(e, neg_tries - e)))
 
 
 def oracle_lines(og, cfg, types, neg_tries, threads):
@@ -80,7 +84,7 @@ def oracle_lines(og, cfg, types, neg_tries, threads):
     from oracle import cuts
 
     res = {}
-    j0 = first_round_draws(cfg.n_neg, neg_tries)
+    j0 = first_round_draws(cfg.n_neg, neg_tries, cfg.batch)
     for qt in types:
         t = time.time()
         q = og.sample(qt, cfg.batch, 0, seed=cfg.seed, threads=threads)
@@ -401,7 +405,7 @@ def summarize_profiles(config, folder, steps):
         if k.startswith(GRAPH_BUILD_KERNELS) or not targs:
             return k
         parts = [x.strip() for x in targs.split(",")]
-        if k in ("k_compact_reg", "k_positive"):   # templated on a count, not a shape
+        if k == "k_positive":                        # templated on a count, not a shape
             return f"{k}<{parts[0]}>"
         if k in ("k_heavy3", "k_units3"):            # the 3p long-list kernel and its units
             return (("k_heavy<3p" if k == "k_heavy3" else "k_units<3p") +
@@ -412,21 +416,12 @@ def summarize_profiles(config, folder, steps):
         return f"{k}<{qt}{', accounting' if acct else ''}{', given candidates' if shared else ''}>"
 
     def tagged(rows):
-        # one round per dispatch (a counter pass has a row per counter)
-        out, rnd, seen = [], defaultdict(lambda: -1), {}
+        # the candidate kernel and what follows it are tagged round 0
+        out = []
         for r in sorted(rows, key=lambda r: int(r["Dispatch_Id"])):
             n = kname(r["Kernel_Name"])
-            if n is None:
-                continue
-            did = r["Dispatch_Id"]
-            if did not in seen:
-                shape = n[n.index("<") + 1:].split(",")[0].rstrip(">") if "<" in n else None
-                if n.startswith(("k_prepare", "k_no_draws")):
-                    rnd[shape] = -1
-                if n.startswith("k_candidates"):
-                    rnd[shape] += 1
-                seen[did] = rnd[shape] if n.startswith(("k_candidates", "k_heavy", "k_units")) else None
-            out.append((n, seen[did], r))
+            if n is not None:
+                out.append((n, 0 if n.startswith(("k_candidates", "k_heavy", "k_units", "k_finish")) else None, r))
         return out
 
     trace = list(csv.DictReader(open(one("**/*kernel_trace.csv"))))
@@ -461,8 +456,7 @@ def summarize_profiles(config, folder, steps):
          "process), then `python3 bench.py --summarize " + folder.rstrip("/")
          + ("" if config == "freebase" else f" --config {config}") + "` to write this file:\n", "```"]
     L += profile_commands(config, steps, os.path.dirname(os.path.normpath(folder)) or ".") + ["```\n"]
-    L.append("Kernels are grouped by name and, for the candidate and long-list kernels, by round of "
-             "candidate draws (round 0 covers the first n_neg + n_neg / 32 + 8 draws). "
+    L.append("Kernels are grouped by name. "
              "\"accounting\" rows are the one untimed pass with the kernels' own read tally.\n")
     L += ["## Durations (kernel trace, all launches of the run)\n",
           "| kernel | round | launches | avg us | median us | total ms |", "|---|---|---|---|---|---|"]
@@ -944,7 +938,7 @@ def main():
             ms = d["candidate_kernel_ms"] if kind == "cand" else d["long_list_kernel_ms"]
         # the events around 3p's long-list work span its batched kernel and its unit kernel
         name = (f"k_candidates<{qt}> r0" if kind == "cand" else
-                "k_heavy<3p> r0 + k_units<3p> r0" if qt == "3p" else f"k_heavy<{qt}> r0")
+                "k_heavy<3p> r0 + k_units<3p> r0" if qt == "3p" else f"k_finish<{qt}> r0")
         tally = acct[qt]["cand_lines" if kind == "cand" else "heavy_lines"] * 64
         algo = None
         if lines:

@@ -225,11 +225,11 @@ int smore_sample_negatives(const smore_graph *g, const smore_query_dag *dag,
                            int64_t *stats, void *workspace, size_t ws_bytes, void *hip_stream);
 
 /* smore_sample_negatives in three parts, for callers that schedule the
-   first round's candidate kernel (the verification of the first batch of
-   rejection-sampling draws, Sec. 3.2) apart from the rest, e.g. the
-   candidate kernels of several calls back to back on one stream:
-   part 0 the per-query preparation, part 1 the first round's candidate
-   kernel, part 2 the rest (long lists, ordered selection, later rounds).
+   candidate kernel (the draws, their verification and the selection of most
+   queries, Sec. 3.2) apart from the rest, e.g. the candidate kernels of
+   several calls back to back on one stream:
+   part 0 the per-query preparation, part 1 the candidate kernel, part 2 the
+   rest (long lists, and the queries that had some).
    Calling parts 0, 1 and 2 with the same arguments, outputs and workspace,
    each after the previous one has completed in stream order (on one stream,
    or ordered by the caller's events across streams), has exactly the effect
@@ -304,10 +304,13 @@ int smore_verify(const smore_graph *g, const smore_query_dag *dag, const smore_s
 
 /* Instrumentation: the next smore_sample or smore_sample_negatives call
    made by this thread records the caller's HIP events (hipEvent_t) on its
-   stream immediately before and after one of its kernels in the first
-   round of candidate draws: which = 0 the candidate kernel, 1 the kernels
-   that intersect long lists (for 3p the batched long-list kernel and the
-   kernel of its units, timed together), 2 the ordered selection.  Each `which` has
+   stream immediately before and after one of its kernels: which = 0 the
+   candidate kernel, 1 the kernels that intersect long lists (for 3p the
+   batched long-list kernel and the kernel of its units, timed together; for
+   the other shapes the finishing kernel), 2 the finishing kernel, which
+   selects the negatives of the queries that had long lists (shapes made of
+   edge tests alone have none of these: both events follow the candidate
+   kernel).  Each `which` has
    its own arm, so one call can time several kernels.  One-shot: the
    next smore_sample, smore_sample_negatives or smore_sample_negatives_part
    call of this thread disarms all of them whether or not they recorded,

@@ -2,8 +2,8 @@
 //
 // Positives (smore_sample_positives), one kernel:
 //
-//  k_positive: PA lanes per query (two; four or eight for plans that
-//    accept less often per attempt), lane l running attempts l, l + PA, ...;
+//  k_positive: PA lanes per query (two for plans that usually accept, up to
+//    64 for the others), lane l running attempts l, l + PA, ...;
 //    the lowest successful attempt wins.
 //    Reverse directional sampling
 //    (Sec. 3.1; appendix on reverse directional sampling): attempt t grounds
@@ -11,29 +11,36 @@
 //    program compiled from the plan, each projection picking an in-relation
 //    of the current entity and an in-neighbour under it.  The first attempt
 //    that reaches every anchor, keeps single-projection siblings apart and
-//    respects max_fanout wins.
+//    respects max_fanout wins.  In a whole call (smore_sample) the same
+//    lanes then look up the query's forward-cached lists.
 //
 // Negatives (smore_sample_negatives): bidirectional rejection sampling
-// (Sec. 3.2) at the node cut the planner picks for the shape, in rounds of
-// candidate draws; k_prepare once, then per round k_candidates, k_heavy
-// and the selection (k_compact_reg, or k_compact for long rounds), all on
-// the caller's stream with no host synchronisation in between (the kernels
-// themselves are described where they are defined).  The three steps can
-// also be launched apart (smore_sample_negatives_part): the preparation,
-// the first round's candidate kernel, the rest.  Forward caching turns
-// the anchors into their neighbour lists A_r(a) (sorted CSR groups, staged
-// in LDS when small, used in place when not); a draw without an in-edge is
-// settled by the in-edge mask (on large graphs a coarse mask, then the
-// entity's in-relation signature, which also settles draws with in-edges
-// under none of the root's relations); the others are verified backward
-// from the candidate; the first occurrences of the non-answers, in draw
-// order, are the negatives, so the output is a function of the draw
-// indices alone.
+// (Sec. 3.2) at the node cut the planner picks for the shape, all on the
+// caller's stream with no host synchronisation:
+//
+//  k_prepare: the forward-cached lists of queries that the call does not
+//    sample itself.
+//  k_candidates: one wavefront per query draws, verifies and selects until
+//    the row is full.  Forward caching turns the anchors into their
+//    neighbour lists A_r(a) (sorted CSR groups, staged in LDS when small,
+//    used in place when not); a draw without an in-edge, or with in-edges
+//    under none of the root's relations, is settled by masks and signatures
+//    that fit the caches; the others are verified backward from the
+//    candidate; the first occurrences of the non-answers, in draw order, are
+//    the negatives, so the output is a function of the draw indices alone.
+//    Edge shapes (1p 2i 3i 2u 2in 3in) end here.
+//  k_heavy3, k_units3 (3p): the candidates with lists too long for one
+//    wavefront to walk.
+//  k_finish: the queries that had such candidates (whose lists it decides
+//    itself for the other shapes): selection and further draws.
+//
+// The steps can also be launched apart (smore_sample_negatives_part): the
+// preparation, the candidate kernel, the rest.
 //
 // Shared-candidate minibatches (smore_sample_shared) and verification of
-// caller candidates (smore_verify) run the same candidate and long-list
-// kernels on given candidates, then pack the states into mask rows
-// (k_shared_set, k_pack).
+// caller candidates (smore_verify) run the same verification on given
+// candidates (k_pairs), each wavefront packing its mask row, then the
+// long-list kernels (k_heavy; 3p as above).
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -502,22 +509,6 @@ __device__ __forceinline__ bool pos_attempt(const GraphView& g, const WalkProgra
 }
 
 // --------------------------------------------------------------- negatives
-// Bidirectional rejection sampling of the negatives, in rounds of candidate
-// draws.  Per round:
-//   k_candidates  one wavefront per query (one-wave workgroups): the round's
-//                 draws, the in-edge mask / signature test, and for the
-//                 survivors either a decision at lane level or a push to the
-//                 heavy queue;
-//   k_heavy       one wavefront per queued (query, draw), persistent
-//                 wavefronts: intersection of a long backward list with the
-//                 forward-cached list(s);
-//   k_compact_reg one wavefront per query (k_compact for rounds of more
-//                 than 1,024 draws): first-occurrence test of every draw so
-//                 far, ordered selection of the first n_neg kept.
-// Queries still short of n_neg after a round go to the next round through a
-// device-side list, each with the draw range the selection sets for it, so
-// rounds need no host synchronisation.
-
 // Lists per shape (anchor slot, relation slot) at the cut the planner picks:
 //   1p {a0}, 2p/3p {V1}, 2i/3i/2u/2in/3in {anchors}, ip/up/inp {Y0, Y1},
 //   pi/pin {V1, a1}, pni {V1 of the complemented chain, a1}.
@@ -611,11 +602,10 @@ constexpr int UNITS_PER_QUERY = 64;
 
 // Workspace carved out of the caller's buffer.
 struct Ws {
-    int32_t* ctrl;    // [0] queue pushes [1] queue pops [2 + k] size of active list k
-                      // [5] 3p units pushed
+    int32_t* ctrl;    // [0] queue pushes [2] queries to finish [5] 3p units pushed
     int32_t* qf;      // [B][QF]: list k at [2k, 2k+1) edge range; [6] bit k: list k staged
     uint8_t* status;  // [B][neg_tries] ST_*
-    int32_t* act[2];  // active query lists
+    int32_t* act[2];  // [0] queries to finish [1] by query: negatives selected so far
     int2* queue;      // (query, draw) items
     int64_t qcap;
     int4* units;      // 3p long-list units: (item, a, b, kind), counted by ctrl[5]
@@ -640,14 +630,12 @@ __device__ __forceinline__ int32_t candidate(const SampleParams& p, int32_t V, i
     return (int32_t)reduce_range(draw64(p.seed, TAG_NEG, q, 0, (uint32_t)j), (uint32_t)V);
 }
 
-// Rounds of candidate draws.  Round 0 takes draws [0, first_round(p)) of
-// every query: n_neg plus a small margin (a query rarely rejects more than
-// a few percent of its draws).  A query still short of n_neg after a round
-// takes its own next range: the draws its deficit needs at the acceptance
-// rate it has had so far, with a margin (next_round_end); the last round
-// takes every query still short to neg_tries.  Rounds are a scheduling
-// detail: a query's negatives are its first n_neg accepted draws in draw
-// order whatever the rounds were.
+// Rounds of candidate draws.  A query first takes n_neg draws plus a small
+// margin (a query rarely rejects more than a few percent of its draws).  One
+// still short of n_neg then takes its own next range: the draws its deficit
+// needs at the acceptance rate it has had so far, with a margin
+// (next_round_end).  Rounds are a scheduling detail: a query's negatives are
+// its first n_neg accepted draws in draw order whatever the rounds were.
 inline int32_t first_margin(const SampleParams& p)
 {
     const int64_t e = (int64_t)p.n_neg + p.n_neg / 32 + 8;
@@ -684,8 +672,8 @@ __device__ __forceinline__ int32_t next_round_end(const SampleParams& p, int32_t
     return (int32_t)(end + more < p.neg_tries ? end + more : p.neg_tries);
 }
 
-// A query's draw range of a later round, kept in its per-query block (two
-// 16-bit draw indices).
+// The draws a query leaves to the finishing kernel, kept in its per-query
+// block (two 16-bit draw indices).
 static_assert(SMORE_MAX_NEG_TRIES < 65536, "draw indices must fit 16 bits");
 __host__ __device__ __forceinline__ int32_t pack_range(int32_t a, int32_t b) { return a | (b << 16); }
 __host__ __device__ __forceinline__ int32_t range_lo(int32_t r) { return r & 0xFFFF; }
@@ -2351,11 +2339,12 @@ int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample
         prof_mark(0, true, st);
     }
     if (!(parts & NEG_REST)) return SMORE_OK;
+    // the finishing kernel is the long-list kernel of every shape but 3p
     prof_mark(1, false, st);
     if constexpr (QT == Q3P) {
         if ((rc = launch_long_lists<QT, T>(gv, p, out, ws, stats, nullptr, st, err))) return rc;
+        prof_mark(1, true, st);
     }
-    prof_mark(1, true, st);
     prof_mark(2, false, st);
     if constexpr (has_long_lists<QT>) {
         // (3p leaves it no long lists: one-wave workgroups, four times as many)
@@ -2364,6 +2353,7 @@ int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample
         if ((rc = check_launch(err))) return rc;
     }
     prof_mark(2, true, st);
+    prof_mark(1, true, st);
     return SMORE_OK;
 }
 

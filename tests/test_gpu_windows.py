@@ -79,3 +79,20 @@ def test_attempt_lanes(qt, batch, max_fanout):
         got = gpu_sample(g, qt, batch, 4, seed=6, pos_tries=pos_tries, max_fanout=max_fanout)
         ref = og.sample(qt, batch, 4, seed=6, pos_tries=pos_tries, max_fanout=max_fanout)
         assert_same(got, ref, what=f"{qt} batch {batch} pos_tries {pos_tries}")
+
+
+# the first test of a draw reads the signatures up to 2^22 entities, the
+# in-edge mask up to 2^24, the coarse mask above
+@pytest.mark.parametrize("V", [1 << 22, (1 << 22) + 1, 1 << 24, (1 << 24) + 1])
+def test_first_test_by_graph_size(V):
+    rng = np.random.default_rng(24)
+    ents = rng.choice(V, 60_000, replace=False).astype(np.int32)
+    ents[:2] = 0, V - 1
+    tr = np.stack([ents[rng.integers(0, len(ents), 200_000)], rng.integers(0, 40, 200_000),
+                   ents[rng.integers(0, len(ents), 200_000)]], axis=1).astype(np.int32)
+    g, og = graph_pair(tr, V, 40, False)
+    for qt in ("1p", "2p", "3p", "2u", "up", "pin"):
+        progress(f"V {V} {qt}")
+        got = gpu_sample(g, qt, 200, 300, seed=7)
+        ref = og.sample(qt, 200, 300, seed=7)
+        assert_same(got, ref, what=f"V {V} {qt}")
