@@ -67,6 +67,7 @@ struct NoTally {
     static constexpr bool on = false;
     __device__ __forceinline__ void read(const void*, int32_t) {}
     __device__ __forceinline__ void bytes_only(int64_t) {}
+    __device__ __forceinline__ void add(const NoTally&) {}
 };
 struct Tally {
     static constexpr bool on = true;
@@ -79,6 +80,7 @@ struct Tally {
         l += ((a + nbytes - 1) >> 6) - (a >> 6) + 1;
     }
     __device__ __forceinline__ void bytes_only(int64_t n) { b += (uint64_t)n; }
+    __device__ __forceinline__ void add(const Tally& o) { b += o.b, l += o.l; }
 };
 
 // Edges [x, y) of v under r when v's node-pointer pair (n0, n1) is known.
@@ -1874,9 +1876,9 @@ __global__ __launch_bounds__(FINISH_WG, 4) void k_finish(GraphView g, SamplePara
                 const bool mine = (lane & 3) == w && k0 + lane < j1 && sv[k0 + lane] == ST_PEND;
                 for (uint64_t m = __ballot(mine); m; m &= m - 1) {
                     const int32_t j = k0 + __ffsll((unsigned long long)m) - 1;
-                    const int2 s = group_range(g.rev, candidate(p, g.V, b, j), chain_r1<QT> ? rel[1] : rel[2], tl);
-                    if constexpr (T::on)
-                        if (lane != 0) tl = T();   // the wave's lookup, charged once
+                    T one;   // the lookup, which every lane makes: charged once
+                    const int2 s = group_range(g.rev, candidate(p, g.V, b, j), chain_r1<QT> ? rel[1] : rel[2], one);
+                    if (lane == 0) tl.add(one);
                     const bool ans = heavy_test<QT>(g, F, rel, make_int2(uni(s.x), uni(s.y)), lane, tl);
                     if (lane == 0) sv[j] = ans ? ST_ANS : ST_NON;
                 }

@@ -1,0 +1,85 @@
+"""The read statistics of smore_sample_negatives (stats) on graphs small enough
+to count every read by hand: bytes of each kind of read, per draw and per
+intersected list."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2110_14890_amd as sm
+from gpu_common import require_gpu, to_numpy
+
+pytestmark = pytest.mark.gpu
+
+TAG_NEG = 2
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def pairs(heads, r, tails):
+    h, t = np.meshgrid(heads, tails, indexing="ij")
+    return np.stack([h.ravel(), np.full(h.size, r), t.ravel()], 1)
+
+
+def run_caller_queries(g, qt, batch, n_neg, neg_tries, seed, anchors, relations, positive):
+    """Rows and statistics of `batch` caller-built queries that are all alike."""
+    import torch
+    dag = sm.query_preset(qt)
+    args = sm.make_args(batch, n_neg, seed=seed, neg_tries=neg_tries)
+    out = sm.alloc_outputs(batch, n_neg)
+    out["anchors"][:] = torch.tensor(anchors, dtype=torch.int32, device="cuda")
+    out["relations"][:] = torch.tensor(relations, dtype=torch.int32, device="cuda")
+    out["positive"][:] = positive
+    stats = torch.zeros((batch, 4), dtype=torch.int64, device="cuda")
+    sm.sample_negatives(g, dag, args, out, stats)
+    return to_numpy(out), stats.cpu().numpy()
+
+
+def search_reads(n):
+    """Reads of one key's bisection in a list of n entries: a probe per
+    halving and the last comparison."""
+    probes = 0
+    while n > 1:
+        n -= n >> 1
+        probes += 1
+    return probes + 1
+
+
+def hub_draws(V, seed, batch, tries, hubs):
+    d = np.array([[oracle.pick(oracle.draw(seed, TAG_NEG, q, 0, j), V) for j in range(tries)]
+                  for q in range(batch)])
+    return np.isin(d, hubs)
+
+
+# Anchors 0 and 1 have the forward lists F0, F1 under relation 0; the
+# candidates of C have the same 2,000 heads under relation 1, none of them in
+# F0 or F1, and nothing else has an in-edge under relation 1.  So of a query's
+# draws exactly those in C go past the first test, each meets a list too long
+# for the wavefront that drew it, and all of them cost the same reads.
+V, HEADS, C = 8192, np.arange(2048, 4048), np.arange(4096, 4496)
+F0, F1 = np.arange(16, 716), np.arange(720, 1520)
+NODE_PAIR, ONE_GROUP = 8, 16     # a node entry and the next; a group and the next
+
+
+@pytest.mark.parametrize("qt", ["2p", "ip", "up"])
+def test_long_lists_are_counted_one_by_one(qt):
+    tr = np.concatenate([pairs([0], 0, F0), pairs([1], 0, F1), pairs(HEADS, 1, C)]).astype(np.int32)
+    g = sm.Graph(tr, V, 2)
+    batch, tries, seed = 64, 300, 11     # one range of draws: [0, tries)
+    two = qt != "2p"
+    out, st = run_caller_queries(g, qt, batch, tries, tries, seed, [0, 1, -1] if two else [0, -1, -1],
+                                 [0, 0, 1] if two else [0, 1, -1], int(C[0]))
+    k = hub_draws(V, seed, batch, tries, C).sum(1)
+    assert k.min() >= 2          # several long lists per query, or nothing is tested
+    lookup = NODE_PAIR + ONE_GROUP
+    cached = lookup + 4 * len(F0) + (lookup + 4 * len(F1) if two else 0)
+    assert np.array_equal(st[:, 0], cached + 4 * tries + lookup * k)
+    # the forward list's entries are the keys, 256 per step (the last step is
+    # padded), each searched in the 2,000 heads; a union searches both lists
+    steps = -(-len(F0) // 256) + (-(-len(F1) // 256) if qt == "up" else 0)
+    searches = 256 * steps * search_reads(len(HEADS))
+    assert np.array_equal(st[:, 2], (lookup + 4 * searches) * k)
+    # a line per probe; the node pair and the group may straddle a line each
+    assert ((searches + 2) * k <= st[:, 3]).all() and (st[:, 3] <= (searches + 4) * k).all()
