@@ -211,10 +211,12 @@ int smore_sample_noalloc(const smore_graph *g, const smore_query_dag *dag,
    writes negatives, n_valid and neg_draws; it may be run on queries built
    by the caller.  stats is NULL or a device int64 [batch, 4] array that
    receives, per query, the bytes and the 64-byte lines of graph data the
-   verification read: [0], [1] in the candidate kernel (forward-cached lists
-   once per query, then every read made from a candidate's side), [2], [3]
-   in the kernel that intersects long lists; lookups inside forward-cached
-   lists are cache hits of the method and are not counted.  Counting makes
+   verification read: [0], [1] by the wavefront that takes the draws
+   (forward-cached lists once per query, then every read made from a
+   candidate's side, whichever kernel takes the draw), [2], [3] in the
+   intersections of lists too long for that wavefront to walk; lookups
+   inside forward-cached lists are cache hits of the method and are not
+   counted.  Counting makes
    the call slower and does not change any other output.  workspace /
    ws_bytes as for smore_sample (smore_sample_positives needs none). */
 int smore_sample_positives(const smore_graph *g, const smore_query_dag *dag,

@@ -1521,7 +1521,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         anc[k] = uni(out.anchors[3 * (int64_t)b + k]);
         rel[k] = uni(out.relations[3 * (int64_t)b + k]);
     }
-    T tl;
+    T tl, tl_long;   // reads of the draws; of the long lists of further draws
     FList F[3];
     int32_t used = 0;
 #pragma unroll
@@ -1755,12 +1755,14 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
                 for (; m; m &= m - 1) {
                     const int32_t i = i0 + __ffsll((unsigned long long)m) - 1;
                     const int32_t c1 = ~uni(L.cand[i]);
-                    T one;
+                    T one;   // the lookup, which every lane makes: charged once
                     const int2 s = group_range(g.rev, c1, chain_r1<QT> ? rel[1] : rel[2], one);
+                    if (lane == 0) tl_long.add(one);
                     FSet whole[3];
 #pragma unroll
                     for (int f = 0; f < 3; ++f) whole[f] = FSet{g.fwd.nbr + F[f].beg, F[f].n};
-                    const bool ans = heavy_test<QT>(g, whole, rel, make_int2(uni(s.x), uni(s.y)), lane, tl);
+                    const bool ans = heavy_test<QT>(g, whole, rel, make_int2(uni(s.x), uni(s.y)), lane,
+                                                    tl_long);
                     if (lane == 0) {
                         L.cand[i] = c1;
                         if (!ans) L.non[i >> 5] |= 1u << (i & 31);
@@ -1813,6 +1815,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         }
     }
     flush_tally(tl, stats, b, lane);
+    if constexpr (MODE == DRAW_FINISH) flush_tally(tl_long, stats, b, lane, 2);
 }
 
 // One query per workgroup: queries differ widely in cost, and the hardware

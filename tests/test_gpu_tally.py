@@ -83,3 +83,27 @@ def test_long_lists_are_counted_one_by_one(qt):
     assert np.array_equal(st[:, 2], (lookup + 4 * searches) * k)
     # a line per probe; the node pair and the group may straddle a line each
     assert ((searches + 2) * k <= st[:, 3]).all() and (st[:, 3] <= (searches + 4) * k).all()
+
+
+# Half of the entities are candidates with 600 heads under relation 1, which
+# hold the forward list: answers.  A query is short after its first range of
+# draws and takes further ones, with long lists of their own.
+@pytest.mark.parametrize("batch", [5, 64, 4096])
+def test_further_draws_are_counted_alike(batch):
+    V, f0, heads, c = 2048, np.arange(16, 536), np.arange(16, 616), np.arange(1024, 2048)
+    tr = np.concatenate([pairs([0], 0, f0), pairs(heads, 1, c)]).astype(np.int32)
+    g = sm.Graph(tr, V, 2)
+    n_neg, tries, seed = 300, 1200, 12
+    out, st = run_caller_queries(g, "2p", batch, n_neg, tries, seed, [0, -1, -1], [0, 1, -1], int(c[0]))
+    rows = min(batch, 64)
+    hub = np.concatenate([np.zeros((rows, 1), int), hub_draws(V, seed, rows, tries, c).cumsum(1)], 1)
+    st, end = st[:rows], out["neg_draws"][:rows]
+    lookup = NODE_PAIR + ONE_GROUP
+    # every list is met within the first 256 of the forward list's entries
+    each = lookup + 4 * 256 * search_reads(len(heads))
+    k = st[:, 2] // each
+    assert (k * each == st[:, 2]).all()
+    taken = (st[:, 0] - (lookup + 4 * len(f0)) - lookup * k) // 4     # draws
+    assert (4 * taken + lookup * k + lookup + 4 * len(f0) == st[:, 0]).all()
+    assert (taken >= end).all() and (taken <= tries).all() and (taken > 400).all()
+    assert np.array_equal(hub[np.arange(rows), taken], k)
