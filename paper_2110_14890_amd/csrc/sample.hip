@@ -966,6 +966,15 @@ __device__ __forceinline__ uint64_t owners_of(bool hit, int owner)
     return res;
 }
 
+// Entry off of the list p[0..len), read by one lane of a step whose next
+// lanes read the entries after it: accounted once per run of lanes, by the
+// lane that holds the list's first entry or starts the step.
+template <class T>
+__device__ __forceinline__ void tally_run(T& tl, const int32_t* p, int32_t off, int32_t len, int lane)
+{
+    if (off == 0 || lane == 0) tl.read(p + off, 4 * min(len - off, 64 - lane));
+}
+
 // Entry k of list f.
 __device__ __forceinline__ int32_t list_entry(const GraphView& g, const WaveLds& L, const FList& F, int32_t k)
 {
@@ -1007,7 +1016,7 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
                 if (on[u]) {
                     if (ln[u] <= nf) {
                         y[u] = g.rev.nbr[st[u] + off[u]];
-                        tl.read(g.rev.nbr + st[u] + off[u], 4);
+                        tally_run(tl, g.rev.nbr + st[u], off[u], ln[u], lane);
                     } else if (QT == QUP && off[u] >= F[0].n) {
                         y[u] = list_entry(g, L, F[1], off[u] - F[0].n);
                     } else {
@@ -1042,12 +1051,13 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
             }
             const bool on = y0 + lane < total;
             const int it = owner_lane(min(y0 + lane, total - 1), ex);
-            const int32_t at = __shfl(start, it) + y0 + lane - __shfl(ex, it);
+            const int32_t yat = y0 + lane - __shfl(ex, it), at = __shfl(start, it) + yat;
+            const int32_t ylen = __shfl(len, it);
             int2 s2 = make_int2(0, 0);
             if (on && !((ans | left) >> it & 1)) {
                 // y without an in-edge under r1's signature class has none under r1
                 const int32_t y = g.rev.nbr[at];
-                tl.read(g.rev.nbr + at, 4);
+                tally_run(tl, g.rev.nbr + at - yat, yat, ylen, lane);
                 tl.read(g.sig + y, 1);
                 const int32_t a0 = g.rev.node[y], a1 = g.rev.node[y + 1];
                 if (g.sig[y] & b1) {
@@ -1074,7 +1084,7 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
                 bool hit = false;
                 if (pi < ptotal && !((ans | left) >> who & 1)) {
                     if (ln <= nf) {
-                        tl.read(g.rev.nbr + lx + off, 4);
+                        tally_run(tl, g.rev.nbr + lx, off, ln, lane);
                         hit = in_list<QT>(g, L, F, 0, g.rev.nbr[lx + off]);
                     } else {
                         hit = has8(g.rev.nbr + lx, ln, list_entry(g, L, F[0], off), true, tl);

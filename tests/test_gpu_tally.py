@@ -107,3 +107,54 @@ def test_further_draws_are_counted_alike(batch):
     assert (4 * taken + lookup * k + lookup + 4 * len(f0) == st[:, 0]).all()
     assert (taken >= end).all() and (taken <= tries).all() and (taken > 400).all()
     assert np.array_equal(hub[np.arange(rows), taken], k)
+
+
+def lines(first, nbytes):
+    """64-byte lines of nbytes from byte offset first of a device array."""
+    return (first + nbytes - 1) // 64 - first // 64 + 1
+
+
+def rev_list(g, node, grp, v):
+    """First edge and length of an entity's only in-group, and the lines of
+    looking it up."""
+    i = int(node[v])
+    assert node[v + 1] == i + 1
+    beg, end = int(grp[i, 1]), int(grp[i + 1, 1])
+    return beg, end - beg, lines(4 * v, NODE_PAIR) + lines(8 * i, ONE_GROUP)
+
+
+# A list that a wavefront walks is one contiguous read of its entries, not a
+# line per entry.  2p: 64 heads per candidate, a forward list of 200 without
+# them; 3p: 16 in-neighbours per candidate with 16 heads each.
+@pytest.mark.parametrize("qt,tries", [("2p", 100), ("3p", 12)])
+def test_walked_lists_are_counted_in_lines(qt, tries):
+    V, batch, seed = 4096, 64, 13
+    f0, c = np.arange(16, 216), np.arange(2048, 2448)
+    if qt == "2p":
+        tr = [pairs([0], 0, f0), pairs(np.arange(512, 576), 1, c)]
+    else:
+        ys = np.arange(600, 616)
+        tr = [pairs([0], 0, f0), pairs(np.arange(512, 528), 1, ys), pairs(ys, 2, c)]
+    g = sm.Graph(np.concatenate(tr).astype(np.int32), V, 3)
+    out, st = run_caller_queries(g, qt, batch, tries, tries, seed, [0, -1, -1],
+                                 [0, 1, -1] if qt == "2p" else [0, 1, 2], int(c[0]))
+    node, grp = g.copy(3, V + 1), g.copy(4, 2 * (g.S_rev + 1)).reshape(-1, 2)
+    draws = [[oracle.pick(oracle.draw(seed, TAG_NEG, q, 0, j), V) for j in range(tries)] for q in range(batch)]
+    checked = 0
+    for q in range(batch):
+        if st[q, 2]:              # lists left to another kernel (more than a wavefront may walk)
+            continue
+        want_b = NODE_PAIR + ONE_GROUP + 4 * len(f0) + 4 * tries
+        want_l = 1 + 1 + lines(0, 4 * len(f0)) + tries
+        hubs = [d for d in draws[q] if d >= c[0] and d <= c[-1]]
+        checked += len(hubs)
+        for d in hubs:
+            beg, n, look = rev_list(g, node, grp, d)
+            want_b += NODE_PAIR + ONE_GROUP + 4 * n
+            want_l += look + lines(4 * beg, 4 * n)
+            for y in ys if qt == "3p" else []:
+                ybeg, yn, ylook = rev_list(g, node, grp, y)
+                want_b += 1 + NODE_PAIR + ONE_GROUP + 4 * yn      # the signature byte first
+                want_l += 1 + ylook + lines(4 * ybeg, 4 * yn)
+        assert (int(st[q, 0]), int(st[q, 1])) == (want_b, want_l), q
+    assert checked > 20
