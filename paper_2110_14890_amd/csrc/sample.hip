@@ -592,7 +592,7 @@ constexpr int CWG = 64;
 constexpr int HEAVY_WG = 256;    // threads of the heavy-queue workgroups
 constexpr int QF = 8;            // int32 per query in the per-query block
 constexpr int PERSIST_BLOCKS = 2048;
-constexpr int FINISH_BLOCKS = 1024;   // workgroups of the finishing kernel
+constexpr int FINISH_WAVES = 4096;    // wavefronts of the finishing kernel: as many as run at once
 // 3p long-list work in bounded units: the long-list kernel expands at most
 // UNIT_Y entities y of an item and searches at most UNIT_PAIRS pairs of one
 // y itself; the rest become units of the unit queue (UNITS_PER_QUERY slots
@@ -941,15 +941,16 @@ __device__ __forceinline__ int32_t excl_prefix(int32_t v, int lane, int32_t* tot
 constexpr int DEEP_LONG = 512, DEEP_TOTAL = 4096, DEEP_STEPS = 12;
 constexpr int DEEP_LEN = 65535;   // lengths are kept in 16 bits; one that long is left
 
-// Drops from np the candidates the pass leaves; returns the lanes dropped.
-__device__ __forceinline__ uint64_t deep_limit(int32_t& np, int lane)
+// Drops from np the candidates the pass leaves (all but `cap` pairs of it);
+// returns the lanes dropped.
+__device__ __forceinline__ uint64_t deep_limit(int32_t& np, int32_t cap, int lane)
 {
     bool over = np > DEEP_LONG;
     if (over) np = 0;
     int32_t tot;
     const int32_t ex = excl_prefix(np, lane, &tot);
-    if (tot > DEEP_TOTAL) {
-        over = over || (np > 0 && ex + np > DEEP_TOTAL);
+    if (tot > cap) {
+        over = over || (np > 0 && ex + np > cap);
         if (over) np = 0;
     }
     return __ballot(over);
@@ -984,7 +985,7 @@ __device__ __forceinline__ int32_t list_entry(const GraphView& g, const WaveLds&
 template <int QT, class T>
 __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds& L, const FList* F,
                                               const int32_t* rel, int32_t start, int32_t len, int lane,
-                                              int32_t& steps, uint64_t* pend, T& tl)
+                                              int32_t cap, int32_t& steps, uint64_t* pend, T& tl)
 {
     uint64_t left = 0, ans = 0;
     if constexpr (QT != Q3P) {
@@ -992,7 +993,7 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
         // for a union of chains)
         const int32_t nf = QT == QUP ? F[0].n + F[1].n : F[0].n;
         int32_t np = len >= DEEP_LEN ? INT_MAX : min(len, nf);
-        left = deep_limit(np, lane);
+        left = deep_limit(np, cap, lane);
         int32_t total;
         const int32_t ex = excl_prefix(np, lane, &total);
         for (int32_t p0 = 0; p0 < total; p0 += 128) {
@@ -1039,7 +1040,7 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
             ans |= owners_of(hit[0], it[0]) | owners_of(hit[1], it[1]);
         }
     } else {
-        left = deep_limit(len, lane);
+        left = deep_limit(len, cap, lane);
         int32_t total;
         const int32_t ex = excl_prefix(len, lane, &total);
         const uint32_t b1 = sig_bit(rel[1]);
@@ -1067,7 +1068,7 @@ __device__ __forceinline__ uint64_t deep_pass(const GraphView& g, const WaveLds&
             }
             const int32_t n2 = s2.y - s2.x;
             int32_t np = min(n2, nf);
-            const uint64_t over = deep_limit(np, lane);
+            const uint64_t over = deep_limit(np, cap, lane);
             if (over) left |= owners_of(over >> lane & 1, it);
             int32_t ptotal;
             const int32_t pex = excl_prefix(np, lane, &ptotal);
@@ -1506,9 +1507,9 @@ __device__ __forceinline__ int32_t select_window(const SampleParams& p, const sm
 
 // Modes of the candidate kernels: the first kernel of a call, which leaves a
 // query with long lists to the long-list kernels and the finishing kernel;
-// the finishing kernel, which decides everything itself; and given
-// candidates (shared or per query), whose verdicts are packed into mask rows.
-enum : int { DRAW_FIRST = 0, DRAW_FINISH = 1, DRAW_GIVEN = 2 };
+// and given candidates (shared or per query), whose verdicts are packed into
+// mask rows.
+enum : int { DRAW_FIRST = 0, DRAW_GIVEN = 1 };
 
 // One query on one wavefront.
 template <int QT, class T, int MODE>
@@ -1531,7 +1532,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         anc[k] = uni(out.anchors[3 * (int64_t)b + k]);
         rel[k] = uni(out.relations[3 * (int64_t)b + k]);
     }
-    T tl, tl_long;   // reads of the draws; of the long lists of further draws
+    T tl;
     FList F[3];
     int32_t used = 0;
 #pragma unroll
@@ -1582,33 +1583,10 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         if (RootRels<QT>::mask >> k & 1) need |= sig_bit(rel[k]);
     int32_t acc = 0, base = 0, end = j_first, cnt = 0;
     bool deferred = false;
-    int32_t steps = MODE == DRAW_FINISH ? INT_MAX : DEEP_STEPS;
+    int32_t steps = DEEP_STEPS;
     int32_t jsel = 0;     // draws [0, jsel) are selected
-    if constexpr (MODE == DRAW_FINISH) {
-        // the draws the first kernel left: their states are settled now
-        acc = uni(ws.act[1][b]);
-        const int32_t rg = uni(qb[7]);
-        base = range_lo(rg);
-        end = range_hi(rg);
-        table_fill(tab, tb.tcap, out.negatives + (int64_t)b * p.n_neg, acc, lane);
-        for (; base < end && acc < p.n_neg;) {
-            const int32_t n = min(end - base, min(WIN, table_room(tb.tcap) - acc));
-            for (int k = 0; 64 * k < n; ++k) {
-                const int32_t i = 64 * k + lane;
-                const bool non = i < n && sv[base + i] == ST_NON;
-                const uint64_t m = __ballot(non);
-                if (i < n) L.cand[i] = candidate(p, g.V, b, base + i);
-                if (lane < 2) L.non[2 * k + lane] = (uint32_t)(m >> (32 * lane));
-            }
-            wave_sync();
-            acc = select_window(p, out, b, L, tab, tb.tcap, base, n, acc, lane);
-            base += n;
-            wave_sync();
-        }
-        end = acc < p.n_neg ? next_round_end(p, base, acc) : base;
-    }
     bool to_stage = used > 0;
-    bool table = MODE == DRAW_FINISH && tb.own;   // the table holds the row so far
+    bool table = false;   // the table holds the row so far
     while (base < end) {
         const int32_t n = MODE == DRAW_GIVEN ? min(end - base, WIN)
                                              : min(end - base, min(WIN, table_room(tb.tcap) - acc));
@@ -1746,7 +1724,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
                     const bool on = at < ndeep;
                     uint64_t over;
                     const uint64_t hit = deep_pass<QT>(g, L, F, rel, on ? L.ds[at] : 0, on ? L.dl[at] : 0,
-                                                       lane, steps, &over, tl);
+                                                       lane, DEEP_TOTAL, steps, &over, tl);
                     // pni: a meeting chain means c is in the complemented set
                     const bool ans = (hit >> lane & 1) != (QT == QPNI);
                     if (on) settle(L.dj[at], over >> lane & 1 ? ST_PEND : ans ? ST_ANS : ST_NON);
@@ -1757,37 +1735,13 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
             if (!more) break;
         }
         const bool any_left = __ballot(left) != 0;
-        if (MODE == DRAW_FINISH && any_left) {
-            // long lists of the finishing kernel: one after the other, the
-            // whole wavefront on each
-            for (int32_t i0 = 0; i0 < n; i0 += 64) {
-                uint64_t m = __ballot(i0 + lane < n && L.cand[i0 + lane] < 0);
-                for (; m; m &= m - 1) {
-                    const int32_t i = i0 + __ffsll((unsigned long long)m) - 1;
-                    const int32_t c1 = ~uni(L.cand[i]);
-                    T one;   // the lookup, which every lane makes: charged once
-                    const int2 s = group_range(g.rev, c1, chain_r1<QT> ? rel[1] : rel[2], one);
-                    if (lane == 0) tl_long.add(one);
-                    FSet whole[3];
-#pragma unroll
-                    for (int f = 0; f < 3; ++f) whole[f] = FSet{g.fwd.nbr + F[f].beg, F[f].n};
-                    const bool ans = heavy_test<QT>(g, whole, rel, make_int2(uni(s.x), uni(s.y)), lane,
-                                                    tl_long);
-                    if (lane == 0) {
-                        L.cand[i] = c1;
-                        if (!ans) L.non[i >> 5] |= 1u << (i & 31);
-                    }
-                }
-            }
-            wave_sync();
-        }
         if constexpr (MODE == DRAW_GIVEN) {
             const int32_t at = (base >> 5) + lane;
             const uint32_t bits = lane < WORDS && 32 * lane < n ? L.non[lane] : 0u;
             if (lane < WORDS && at < words) mask[(int64_t)b * words + at] = bits;
             cnt += __popc(bits);
         } else {
-            deferred = deferred || (MODE == DRAW_FIRST && any_left);
+            deferred = deferred || any_left;
             if (deferred) {
                 for (int32_t i = lane; i < n; i += 64)
                     sv[base + i] = L.non[i >> 5] >> (i & 31) & 1u ? ST_NON
@@ -1825,7 +1779,6 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         }
     }
     flush_tally(tl, stats, b, lane);
-    if constexpr (MODE == DRAW_FINISH) flush_tally(tl_long, stats, b, lane, 2);
 }
 
 // One query per workgroup: queries differ widely in cost, and the hardware
@@ -1849,60 +1802,6 @@ __global__ __launch_bounds__(CWG, 4) void k_pairs(GraphView g, SampleParams p, s
     const int32_t n = p.n_shared ? min(p.n_neg, uni(*p.n_shared)) : p.n_neg;
     query_draws<QT, NoTally, DRAW_GIVEN>(g, p, out, ws, nullptr, mask, Table{0, 0}, nullptr, L,
                                          blockIdx.x, n, threadIdx.x);
-}
-
-// The queries that had long lists among their first draws: their verdicts
-// (for 3p the long-list kernels have settled them), selection, and whatever
-// further draws the queries need.  Persistent workgroups of four wavefronts
-// over the list: the long lists of a query are dealt over the four, the rest
-// is the first one's.  (A kernel of its own for the long lists was a launch
-// of 4 to 16 us for a few queries.)
-constexpr int FINISH_WG = 256;
-template <int QT, class T>
-__global__ __launch_bounds__(FINISH_WG, 4) void k_finish(GraphView g, SampleParams p, smore_sample_out out,
-                                                         Ws ws, int64_t* stats, Table tb)
-{
-    __shared__ WaveLds L;
-    extern __shared__ __align__(16) int32_t own_tab[];
-    const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
-    const int32_t n = uni(ws.ctrl[2]);
-    for (int32_t qi = blockIdx.x; qi < n; qi += gridDim.x) {
-        const int32_t b = uni(ws.act[0][qi]);
-        if constexpr (QT != Q3P) {
-            const int32_t* qb = ws.qf + (int64_t)b * QF;
-            const int32_t j0 = range_lo(uni(qb[7])), j1 = range_hi(uni(qb[7]));
-            uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
-            int32_t rel[3];
-            FSet F[3];
-            T tl;
-#pragma unroll
-            for (int f = 0; f < 3; ++f) {
-                rel[f] = uni(out.relations[3 * (int64_t)b + f]);
-                F[f] = FSet{nullptr, 0};
-                if (f < Shape<QT>::nf) {
-                    const int32_t beg = uni(qb[2 * f]);
-                    F[f] = FSet{g.fwd.nbr + beg, uni(qb[2 * f + 1]) - beg};
-                }
-            }
-            for (int32_t k0 = j0; k0 < j1; k0 += 64) {
-                // every fourth draw: no wavefront reads a state that another one writes
-                const bool mine = (lane & 3) == w && k0 + lane < j1 && sv[k0 + lane] == ST_PEND;
-                for (uint64_t m = __ballot(mine); m; m &= m - 1) {
-                    const int32_t j = k0 + __ffsll((unsigned long long)m) - 1;
-                    T one;   // the lookup, which every lane makes: charged once
-                    const int2 s = group_range(g.rev, candidate(p, g.V, b, j), chain_r1<QT> ? rel[1] : rel[2], one);
-                    if (lane == 0) tl.add(one);
-                    const bool ans = heavy_test<QT>(g, F, rel, make_int2(uni(s.x), uni(s.y)), lane, tl);
-                    if (lane == 0) sv[j] = ans ? ST_ANS : ST_NON;
-                }
-            }
-            flush_tally(tl, stats, b, lane, 2);
-            __syncthreads();
-        }
-        if (w == 0)
-            query_draws<QT, T, DRAW_FINISH>(g, p, out, ws, stats, nullptr, tb, own_tab, L, b, 0, lane);
-        __syncthreads();
-    }
 }
 
 // Verdict of a queued pair by the long-list kernels: its state, or for given
@@ -2236,6 +2135,198 @@ __global__ __launch_bounds__(HEAVY_WG) void k_units3(GraphView g, SampleParams p
     }
 }
 
+// ------------------------------------------------------ finishing kernel
+// A query's anchors, relations and forward lists, which are read in place.
+struct QueryLists {
+    int32_t anc[3], rel[3];
+    FList F[3];
+};
+
+template <int QT>
+__device__ __forceinline__ QueryLists query_lists(const smore_sample_out& out, const Ws& ws, int32_t b)
+{
+    const int32_t* qb = ws.qf + (int64_t)b * QF;
+    QueryLists q;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+        q.anc[f] = uni(out.anchors[3 * (int64_t)b + f]);
+        q.rel[f] = uni(out.relations[3 * (int64_t)b + f]);
+        q.F[f] = FList{0, 0, 0, false};
+        if (f >= Shape<QT>::nf) continue;
+        q.F[f].beg = uni(qb[2 * f]);
+        q.F[f].n = uni(qb[2 * f + 1]) - q.F[f].beg;
+    }
+    return q;
+}
+
+// States of the draws [j, j + 64) below j1, one per lane: what the candidate
+// kernel does with them, but for 3p every candidate with a backward list is
+// left pending.
+template <int QT, class T>
+__device__ __forceinline__ void finish_draws(const GraphView& g, const SampleParams& p, const WaveLds& L,
+                                             const QueryLists& q, int32_t b, int32_t j, int32_t j1,
+                                             uint8_t* sv, int lane, T& tl)
+{
+    j += lane;
+    uint32_t need = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (RootRels<QT>::mask >> k & 1) need |= sig_bit(q.rel[k]);
+    int32_t c[2] = {0, 0}, st[2] = {ST_NON, ST_NON};
+    bool act[2] = {false, false};
+    int2 lst[2] = {make_int2(0, 0), make_int2(0, 0)};
+    if (j < j1) {
+        c[0] = candidate(p, g.V, b, j);
+        tl.read(g.has_in + (c[0] >> 5), 4);
+        bool in = true;
+        if (g.first_test == TEST_MASK) in = g.has_in[c[0] >> 5] >> (c[0] & 31) & 1u;
+        if (g.first_test == TEST_MASK4) in = g.has_in4[c[0] >> 7] >> (c[0] >> 2 & 31) & 1u;
+        const uint32_t sg = in ? (uint32_t)g.sig[c[0]] : 0u;
+        act[0] = RootRels<QT>::any ? (sg & need) != 0 : (sg & need) == need;
+    }
+    shallow_test2<QT>(g, L, q.F, q.anc, q.rel, c, act, st, lst, tl);
+    if (!act[0]) st[0] = ST_NON;
+    const bool deep = act[0] && st[0] == ST_DEEP;
+    if constexpr (QT == Q3P) {
+        if (deep) st[0] = ST_PEND;
+    } else if (__ballot(deep)) {
+        int32_t steps = INT_MAX;
+        uint64_t over;
+        const uint64_t hit = deep_pass<QT>(g, L, q.F, q.rel, lst[0].x, deep ? lst[0].y - lst[0].x : 0, lane,
+                                           INT_MAX, steps, &over, tl);
+        if (deep) st[0] = over >> lane & 1 ? ST_PEND : (hit >> lane & 1) != (QT == QPNI) ? ST_ANS : ST_NON;
+    }
+    if (j < j1) sv[j] = (uint8_t)st[0];
+}
+
+// Verdicts of up to 64 pending draws, one per lane (on: the lane has one).
+// Their lists are looked up side by side; for 3p all entities and pairs are
+// laid out over the lanes, for the other shapes the pairs of the lists a
+// wavefront may walk, and the others are met one after the other.
+template <int QT, class T>
+__device__ __forceinline__ void finish_pending(const GraphView& g, const SampleParams& p, Ws& ws,
+                                               const WaveLds& L, const QueryLists& q, int32_t b, int32_t j,
+                                               bool on, uint8_t* sv, int lane, T& tl)
+{
+    int2 s = make_int2(0, 0);
+    if (on) s = group_range(g.rev, candidate(p, g.V, b, j), q.rel[chain_r1<QT> ? 1 : 2], tl);
+    uint64_t ans;
+    if constexpr (QT == Q3P) {
+        Slice3 w;
+        w.valid = on;
+        w.b = b;
+        w.j = j;
+        w.r1 = q.rel[1];
+        w.f0b = q.F[0].beg;
+        w.f0n = q.F[0].n;
+        w.sx = s.x;
+        w.y1 = s.y - s.x;
+        w.k1 = INT_MAX;
+        ans = decide_slices3<false>(g, ws, w, -1, lane, tl);
+    } else {
+        int32_t steps = INT_MAX;
+        uint64_t over;
+        ans = deep_pass<QT>(g, L, q.F, q.rel, s.x, s.y - s.x, lane, INT_MAX, steps, &over, tl);
+        if (QT == QPNI) ans = ~ans & ~over;
+        FSet F[3];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) F[f] = FSet{g.fwd.nbr + q.F[f].beg, q.F[f].n};
+        for (; over; over &= over - 1) {
+            const int k = __ffsll((unsigned long long)over) - 1;
+            if (heavy_test<QT>(g, F, q.rel, make_int2(readlane(s.x, k), readlane(s.y, k)), lane, tl))
+                ans |= 1ull << k;
+        }
+    }
+    if (on) sv[j] = ans >> lane & 1 ? ST_ANS : ST_NON;
+}
+
+// The queries that had long lists among their first draws: their verdicts
+// (for 3p the long-list kernels have settled them), selection, and whatever
+// further draws the queries need, a range at a time.  A workgroup takes a
+// query: draws and pending lists are dealt over its wavefronts, selection is
+// the first one's.  (A kernel of its own for the long lists was a launch of
+// 4 to 16 us for a few queries.)
+template <int QT, class T>
+__global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, smore_sample_out out, Ws ws,
+                                                 int64_t* stats, Table tb)
+{
+    __shared__ WaveLds L;
+    __shared__ uint16_t items[SMORE_MAX_NEG_TRIES];   // pending draws of the range
+    __shared__ int32_t n_items, next[2];
+    extern __shared__ __align__(16) int32_t own_tab[];
+    int32_t* tab = tb.own ? own_tab : (int32_t*)&L;
+    const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), nw = blockDim.x >> 6;
+    const int32_t n = uni(ws.ctrl[2]);
+    for (int32_t qi = blockIdx.x; qi < n; qi += gridDim.x) {
+        const int32_t b = uni(ws.act[0][qi]);
+        const QueryLists q = query_lists<QT>(out, ws, b);
+        const int32_t range = uni(ws.qf[(int64_t)b * QF + 7]);
+        uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
+        int32_t* row = out.negatives + (int64_t)b * p.n_neg;
+        int32_t j0 = range_lo(range), j1 = range_hi(range), acc = uni(ws.act[1][b]);
+        T tl;
+        if (w == 0) table_fill(tab, tb.tcap, row, acc, lane);
+        for (bool first = true; j0 < j1; first = false) {
+            if (!first) {
+                for (int32_t j = j0 + 64 * w; j < j1; j += 64 * nw)
+                    finish_draws<QT>(g, p, L, q, b, j, j1, sv, lane, tl);
+                flush_tally(tl, stats, b, lane);
+            }
+            if (QT != Q3P || !first) {
+                if (tid == 0) n_items = 0;
+                __syncthreads();
+                for (int32_t j = j0 + tid; j < j1; j += blockDim.x)
+                    if (sv[j] == ST_PEND) items[atomicAdd(&n_items, 1)] = (uint16_t)j;
+                __syncthreads();
+                const int32_t m = uni(n_items), each = min(64, (m + nw - 1) / nw);
+                for (int32_t k = each * w; k < m; k += each * nw) {
+                    const bool on = lane < each && k + lane < m;
+                    finish_pending<QT>(g, p, ws, L, q, b, on ? items[k + lane] : 0, on, sv, lane, tl);
+                }
+                flush_tally(tl, stats, b, lane, 2);
+                __syncthreads();
+            }
+            if (w == 0) {
+                while (j0 < j1 && acc < p.n_neg) {
+                    const int32_t m = min(j1 - j0, min(WIN, table_room(tb.tcap) - acc));
+                    for (int k = 0; 64 * k < m; ++k) {
+                        const int32_t i = 64 * k + lane;
+                        const bool non = i < m && sv[j0 + i] == ST_NON;
+                        const uint64_t bits = __ballot(non);
+                        if (i < m) L.cand[i] = candidate(p, g.V, b, j0 + i);
+                        if (lane < 2) L.non[2 * k + lane] = (uint32_t)(bits >> (32 * lane));
+                    }
+                    wave_sync();
+                    acc = select_window(p, out, b, L, tab, tb.tcap, j0, m, acc, lane);
+                    j0 += m;
+                    wave_sync();
+                }
+                if (lane == 0) {
+                    next[0] = j0;
+                    next[1] = j0;
+                    if (acc < p.n_neg) {
+                        // where the GPU is not full, a range that the workgroup's wavefronts
+                        // take at once costs no more than a shorter one
+                        const int32_t least = 2 * n <= (int32_t)gridDim.x ? j0 + 64 * nw : j0;
+                        next[1] = min(max(next_round_end(p, j0, acc), least), p.neg_tries);
+                    }
+                }
+            }
+            __syncthreads();
+            j0 = uni(next[0]);
+            j1 = uni(next[1]);
+        }
+        if (w == 0) {
+            for (int32_t k = acc + lane; k < p.n_neg; k += 64) row[k] = -1;
+            if (lane == 0) {
+                out.n_valid[b] = acc;
+                if (acc < p.n_neg) out.neg_draws[b] = p.neg_tries;
+            }
+        }
+        __syncthreads();   // the next query takes the table and the list
+    }
+}
+
 __device__ __forceinline__ void ht_insert(int32_t* tv, int32_t* tj, uint32_t mask, int shift,
                                           int32_t c, int32_t j)
 {
@@ -2304,6 +2395,21 @@ inline void prof_mark(int which, bool after, hipStream_t st)
     if (after) a = ProfileArm{};
 }
 
+// Wavefronts per query of the finishing kernel: as many as run at once, 4 to
+// 16, since a call of few queries would otherwise last as long as one
+// wavefront takes for all draws and lists of the worst query (16 queries x
+// 1,000 negatives on a graph of 2,000 entities and 300,000 triples, where most
+// candidates are answers: one wavefront for the draws 32.3 ms for 3p and 3.7
+// for 2p, sixteen 1.5 and 0.6).  3p leaves it no lists of the first draws:
+// calls that fill the GPU run one (Freebase-shaped step 598 us, with four 612).
+template <int QT>
+inline int finish_waves(const SampleParams& p)
+{
+    if (p.batch <= FINISH_WAVES / 16) return 16;
+    if (p.batch <= FINISH_WAVES / 8) return 8;
+    return QT == Q3P && p.batch >= FINISH_WAVES ? 1 : 4;
+}
+
 // The long-list kernels over the queue (mask: see put_verdict).
 template <int QT, class T>
 int launch_long_lists(const GraphView& gv, const SampleParams& p, const smore_sample_out& out, Ws ws,
@@ -2362,9 +2468,8 @@ int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample
     }
     prof_mark(2, false, st);
     if constexpr (has_long_lists<QT>) {
-        // (3p leaves it no long lists: one-wave workgroups, four times as many)
-        const int wg = QT == Q3P ? 64 : FINISH_WG;
-        k_finish<QT, T><<<min(p.batch, FINISH_BLOCKS * FINISH_WG / wg), wg, own, st>>>(gv, p, out, ws, stats, tb);
+        const int nw = finish_waves<QT>(p);
+        k_finish<QT, T><<<min(p.batch, FINISH_WAVES / nw), 64 * nw, own, st>>>(gv, p, out, ws, stats, tb);
         if ((rc = check_launch(err))) return rc;
     }
     prof_mark(2, true, st);
