@@ -605,9 +605,11 @@ constexpr int UNITS_PER_QUERY = 64;
 // Workspace carved out of the caller's buffer.
 struct Ws {
     int32_t* ctrl;    // [0] queue pushes [2] queries to finish [5] 3p units pushed
-    int32_t* qf;      // [B][QF]: list k at [2k, 2k+1) edge range; [6] bit k: list k staged
+    int32_t* qf;      // [B][QF]: list k at [2k, 2k+1) edge range; [6] bit k: list k staged,
+                      // [7] the draws of a query to finish
     uint8_t* status;  // [B][neg_tries] ST_*
-    int32_t* act[2];  // [0] queries to finish [1] by query: negatives selected so far
+    int32_t* act[2];  // [0] queries to finish [1] by query: negatives selected so far (and from
+                      // bit 16 on the finishing workgroups that are done with its first range)
     int2* queue;      // (query, draw) items
     int64_t qcap;
     int4* units;      // 3p long-list units: (item, a, b, kind), counted by ctrl[5]
@@ -680,6 +682,22 @@ static_assert(SMORE_MAX_NEG_TRIES < 65536, "draw indices must fit 16 bits");
 __host__ __device__ __forceinline__ int32_t pack_range(int32_t a, int32_t b) { return a | (b << 16); }
 __host__ __device__ __forceinline__ int32_t range_lo(int32_t r) { return r & 0xFFFF; }
 __host__ __device__ __forceinline__ int32_t range_hi(int32_t r) { return (int32_t)((uint32_t)r >> 16); }
+
+// The draw at which a query's row is likely to be full, given the non-answers
+// `non`, answers `ans` and pending candidates `pend` of its first `base` draws:
+// base when these should do.  Where answers were met, the pending ones are
+// taken for answers mostly.  n_neg distinct non-answers of V * a take
+// -V ln(1 - n_neg / (V a)) draws.
+__device__ __forceinline__ int32_t likely_end(const SampleParams& p, int32_t V, int32_t base, int32_t non,
+                                              int32_t ans, int32_t pend)
+{
+    const float a = ((float)non + (float)pend / (float)(ans + 1)) / (float)base;
+    const float x = (float)p.n_neg / ((float)V * a);
+    if (!(x < 0.99f)) return p.neg_tries;
+    const float d = -(float)V * log1pf(-x);
+    if (d <= (float)base) return base;
+    return d * 1.1f + 16.0f < (float)p.neg_tries ? (int32_t)(d * 1.1f) + 16 : p.neg_tries;
+}
 
 size_t ws_layout(const SampleParams& p, Ws* w, char* base)
 {
@@ -2159,13 +2177,31 @@ __device__ __forceinline__ QueryLists query_lists(const smore_sample_out& out, c
     return q;
 }
 
+// A query's states, written and read by several workgroups (shared) or by
+// one.  Shared ones go past the L2, which other workgroups have their own of,
+// so that no fence has to empty it: with fences the 64 queries x 16 negatives
+// of 2p on a dense graph took 160 us, without 60.
+struct States {
+    uint8_t* p;
+    bool shared;
+    __device__ __forceinline__ int32_t get(int32_t j) const
+    {
+        return shared ? __hip_atomic_load(p + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : p[j];
+    }
+    __device__ __forceinline__ void put(int32_t j, int32_t st) const
+    {
+        if (shared) __hip_atomic_store(p + j, (uint8_t)st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else p[j] = (uint8_t)st;
+    }
+};
+
 // States of the draws [j, j + 64) below j1, one per lane: what the candidate
 // kernel does with them, but for 3p every candidate with a backward list is
 // left pending.
 template <int QT, class T>
 __device__ __forceinline__ void finish_draws(const GraphView& g, const SampleParams& p, const WaveLds& L,
                                              const QueryLists& q, int32_t b, int32_t j, int32_t j1,
-                                             uint8_t* sv, int lane, T& tl)
+                                             const States& sv, int lane, T& tl)
 {
     j += lane;
     uint32_t need = 0;
@@ -2196,7 +2232,7 @@ __device__ __forceinline__ void finish_draws(const GraphView& g, const SamplePar
                                            INT_MAX, steps, &over, tl);
         if (deep) st[0] = over >> lane & 1 ? ST_PEND : (hit >> lane & 1) != (QT == QPNI) ? ST_ANS : ST_NON;
     }
-    if (j < j1) sv[j] = (uint8_t)st[0];
+    if (j < j1) sv.put(j, st[0]);
 }
 
 // Verdicts of up to 64 pending draws, one per lane (on: the lane has one).
@@ -2206,7 +2242,7 @@ __device__ __forceinline__ void finish_draws(const GraphView& g, const SamplePar
 template <int QT, class T>
 __device__ __forceinline__ void finish_pending(const GraphView& g, const SampleParams& p, Ws& ws,
                                                const WaveLds& L, const QueryLists& q, int32_t b, int32_t j,
-                                               bool on, uint8_t* sv, int lane, T& tl)
+                                               bool on, const States& sv, int lane, T& tl)
 {
     int2 s = make_int2(0, 0);
     if (on) s = group_range(g.rev, candidate(p, g.V, b, j), q.rel[chain_r1<QT> ? 1 : 2], tl);
@@ -2237,7 +2273,7 @@ __device__ __forceinline__ void finish_pending(const GraphView& g, const SampleP
                 ans |= 1ull << k;
         }
     }
-    if (on) sv[j] = ans >> lane & 1 ? ST_ANS : ST_NON;
+    if (on) sv.put(j, ans >> lane & 1 ? ST_ANS : ST_NON);
 }
 
 // The queries that had long lists among their first draws: their verdicts
@@ -2245,53 +2281,98 @@ __device__ __forceinline__ void finish_pending(const GraphView& g, const SampleP
 // further draws the queries need, a range at a time.  A workgroup takes a
 // query: draws and pending lists are dealt over its wavefronts, selection is
 // the first one's.  (A kernel of its own for the long lists was a launch of
-// 4 to 16 us for a few queries.)
+// 4 to 16 us for a few queries.)  Where the workgroups outnumber the queries,
+// several share a query's first range, and with it the further draws it is
+// likely to need; the last one to be done with its share goes on alone.
 template <int QT, class T>
 __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, smore_sample_out out, Ws ws,
                                                  int64_t* stats, Table tb)
 {
     __shared__ WaveLds L;
     __shared__ uint16_t items[SMORE_MAX_NEG_TRIES];   // pending draws of the range
-    __shared__ int32_t n_items, next[2];
+    __shared__ int32_t n_items, count[2], next[2];
     extern __shared__ __align__(16) int32_t own_tab[];
     int32_t* tab = tb.own ? own_tab : (int32_t*)&L;
     const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), nw = blockDim.x >> 6;
     const int32_t n = uni(ws.ctrl[2]);
-    for (int32_t qi = blockIdx.x; qi < n; qi += gridDim.x) {
-        const int32_t b = uni(ws.act[0][qi]);
+    // workgroups per query: one where the call fills the GPU
+    const int32_t per = nw > 4 && n < (int32_t)gridDim.x ? gridDim.x / max(n, 1) : 1;
+    for (int32_t task = blockIdx.x; task < n * per; task += gridDim.x) {
+        const int32_t b = uni(ws.act[0][task / per]);
+        int32_t share = task % per;
         const QueryLists q = query_lists<QT>(out, ws, b);
         const int32_t range = uni(ws.qf[(int64_t)b * QF + 7]);
-        uint8_t* sv = ws.status + (int64_t)b * p.neg_tries;
         int32_t* row = out.negatives + (int64_t)b * p.n_neg;
-        int32_t j0 = range_lo(range), j1 = range_hi(range), acc = uni(ws.act[1][b]);
-        T tl;
-        if (w == 0) table_fill(tab, tb.tcap, row, acc, lane);
-        for (bool first = true; j0 < j1; first = false) {
-            if (!first) {
-                for (int32_t j = j0 + 64 * w; j < j1; j += 64 * nw)
-                    finish_draws<QT>(g, p, L, q, b, j, j1, sv, lane, tl);
-                flush_tally(tl, stats, b, lane);
+        int32_t j0 = range_lo(range), mid = range_hi(range), j1 = mid;
+        int32_t acc = uni(ws.act[1][b]) & 0xFFFF;
+        int32_t shares = 1;
+        if (per > 1) {
+            if (tid < 2) count[tid] = 0;
+            __syncthreads();
+            int32_t non = 0, pend = 0;
+            for (int32_t j = j0 + 64 * w; j < j1; j += 64 * nw) {
+                const int32_t st = j + lane < j1 ? ws.status[(int64_t)b * p.neg_tries + j + lane] : ST_ANS;
+                non += __popcll(__ballot(st == ST_NON));
+                pend += __popcll(__ballot(st == ST_PEND));
             }
-            if (QT != Q3P || !first) {
+            if (lane == 0) {
+                atomicAdd(&count[0], non);
+                atomicAdd(&count[1], pend);
+            }
+            __syncthreads();
+            non = uni(count[0]);
+            pend = uni(count[1]);
+            j1 = likely_end(p, g.V, mid, acc + non, mid - j0 - non - pend, pend);
+            shares = min(per, max(1, (pend + j1 - mid + nw - 1) / nw));   // a wavefront has work in each
+        }
+        if (share >= shares) continue;
+        const States sv{ws.status + (int64_t)b * p.neg_tries, shares > 1};
+        bool first = true;
+        T tl;
+        for (;;) {
+            // states of the draws [mid, j1) and verdicts of the pending ones of
+            // [j0, j1): runs of `each` draws, dealt over shares and wavefronts
+            const int32_t each = shares > 1 ? min(64, max(1, (j1 - j0) / (shares * nw))) : 64;
+            for (int32_t r = share + shares * w; mid < j1 && j0 + r * each < j1; r += shares * nw) {
+                const int32_t ja = max(j0 + r * each, mid), jb = min(j0 + (r + 1) * each, j1);
+                if (ja < jb) finish_draws<QT>(g, p, L, q, b, ja, jb, sv, lane, tl);
+            }
+            flush_tally(tl, stats, b, lane);
+            if (QT != Q3P || mid < j1) {
                 if (tid == 0) n_items = 0;
                 __syncthreads();
-                for (int32_t j = j0 + tid; j < j1; j += blockDim.x)
-                    if (sv[j] == ST_PEND) items[atomicAdd(&n_items, 1)] = (uint16_t)j;
+                for (int32_t k = tid;; k += blockDim.x) {
+                    const int32_t r = share + shares * (k / each), j = j0 + r * each + k % each;
+                    if (j0 + r * each >= j1) break;
+                    if (j < j1 && sv.get(j) == ST_PEND) items[atomicAdd(&n_items, 1)] = (uint16_t)j;
+                }
                 __syncthreads();
-                const int32_t m = uni(n_items), each = min(64, (m + nw - 1) / nw);
-                for (int32_t k = each * w; k < m; k += each * nw) {
-                    const bool on = lane < each && k + lane < m;
+                const int32_t m = uni(n_items), mine = min(64, (m + nw - 1) / nw);
+                for (int32_t k = mine * w; k < m; k += mine * nw) {
+                    const bool on = lane < mine && k + lane < m;
                     finish_pending<QT>(g, p, ws, L, q, b, on ? items[k + lane] : 0, on, sv, lane, tl);
                 }
                 flush_tally(tl, stats, b, lane, 2);
-                __syncthreads();
             }
+            if (shares > 1) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);   // each wavefront's states are written when its workgroup counts
+                __syncthreads();
+                if (tid == 0) next[0] = atomicAdd(&ws.act[1][b], 1 << 16) >> 16;
+                __syncthreads();
+                if (uni(next[0]) + 1 < shares) break;
+                share = 0;
+                shares = 1;
+            }
+            __syncthreads();
             if (w == 0) {
+                if (first) table_fill(tab, tb.tcap, row, acc, lane);
+                first = false;
                 while (j0 < j1 && acc < p.n_neg) {
                     const int32_t m = min(j1 - j0, min(WIN, table_room(tb.tcap) - acc));
                     for (int k = 0; 64 * k < m; ++k) {
                         const int32_t i = 64 * k + lane;
-                        const bool non = i < m && sv[j0 + i] == ST_NON;
+                        const bool non = i < m && sv.get(j0 + i) == ST_NON;
                         const uint64_t bits = __ballot(non);
                         if (i < m) L.cand[i] = candidate(p, g.V, b, j0 + i);
                         if (lane < 2) L.non[2 * k + lane] = (uint32_t)(bits >> (32 * lane));
@@ -2303,25 +2384,24 @@ __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, sm
                 }
                 if (lane == 0) {
                     next[0] = j0;
-                    next[1] = j0;
-                    if (acc < p.n_neg) {
-                        // where the GPU is not full, a range that the workgroup's wavefronts
-                        // take at once costs no more than a shorter one
-                        const int32_t least = 2 * n <= (int32_t)gridDim.x ? j0 + 64 * nw : j0;
-                        next[1] = min(max(next_round_end(p, j0, acc), least), p.neg_tries);
-                    }
+                    // where the GPU is not full, a range that the workgroup's wavefronts
+                    // take at once costs no more than a shorter one
+                    const int32_t least = 2 * n <= (int32_t)gridDim.x ? j0 + 64 * nw : j0;
+                    next[1] = acc < p.n_neg ? min(max(next_round_end(p, j0, acc), least), p.neg_tries) : j0;
                 }
             }
             __syncthreads();
-            j0 = uni(next[0]);
+            j0 = mid = uni(next[0]);
             j1 = uni(next[1]);
-        }
-        if (w == 0) {
-            for (int32_t k = acc + lane; k < p.n_neg; k += 64) row[k] = -1;
-            if (lane == 0) {
-                out.n_valid[b] = acc;
-                if (acc < p.n_neg) out.neg_draws[b] = p.neg_tries;
+            if (j0 < j1) continue;
+            if (w == 0) {
+                for (int32_t k = acc + lane; k < p.n_neg; k += 64) row[k] = -1;
+                if (lane == 0) {
+                    out.n_valid[b] = acc;
+                    if (acc < p.n_neg) out.neg_draws[b] = p.neg_tries;
+                }
             }
+            break;
         }
         __syncthreads();   // the next query takes the table and the list
     }
@@ -2469,7 +2549,7 @@ int run_negatives(const GraphView& gv, const SampleParams& p, const smore_sample
     prof_mark(2, false, st);
     if constexpr (has_long_lists<QT>) {
         const int nw = finish_waves<QT>(p);
-        k_finish<QT, T><<<min(p.batch, FINISH_WAVES / nw), 64 * nw, own, st>>>(gv, p, out, ws, stats, tb);
+        k_finish<QT, T><<<FINISH_WAVES / nw, 64 * nw, own, st>>>(gv, p, out, ws, stats, tb);
         if ((rc = check_launch(err))) return rc;
     }
     prof_mark(2, true, st);

@@ -7,6 +7,7 @@ import pytest
 import kgsynth
 import paper_2110_14890_amd as sm
 from gpu_common import assert_same, gpu_sample, graph_pair, progress, require_gpu
+from test_gpu_parity import hub_graph_3p
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +58,28 @@ def test_small_calls_are_spread_over_the_gpu(qt):
     few, many = call_ms(g, qt, 16, 1000), call_ms(g, qt, 1024, 1000)
     progress(f"{qt}: 16 queries {few:.2f} ms, 1,024 queries {many:.2f} ms")
     assert few < 0.5 * many
+
+
+# the lists of hubs, and of 3p the units, where several workgroups share a query
+@pytest.mark.parametrize("qt", LONG)
+def test_few_queries_on_hub_graph(qt):
+    tr, V, R = hub_graph_3p()
+    extra = np.stack([np.full(400, 5), np.zeros(400, int), np.arange(2500, 2900)], 1)
+    tr = np.concatenate([tr, extra.astype(np.int32)])
+    g, og = graph_pair(tr, V, R)
+    for batch, n_neg, tries in [(1, 40, 160), (12, 500, 2000), (130, 3900, 4096)]:
+        progress(f"hub {qt} batch {batch}")
+        got = gpu_sample(g, qt, batch, n_neg, seed=8, neg_tries=tries)
+        ref = og.sample(qt, batch, n_neg, seed=8, neg_tries=tries)
+        assert_same(got, ref, what=f"hub {qt} batch {batch}")
+
+
+# one query cannot be dealt over workgroups but by its draws: its call stays
+# near that of 256 of them
+@pytest.mark.parametrize("qt", ["2p", "ip"])
+def test_one_query_is_shared_by_workgroups(qt):
+    rng = np.random.default_rng(42)
+    g = sm.Graph(kgsynth.random_tiny(rng, 2000, 3, 300000), 2000, 3)
+    one, many = call_ms(g, qt, 4, 1000), call_ms(g, qt, 256, 1000)
+    progress(f"{qt}: 4 queries {one:.2f} ms, 256 queries {many:.2f} ms")
+    assert one < 0.6 * many
