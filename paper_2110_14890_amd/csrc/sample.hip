@@ -606,7 +606,8 @@ constexpr int UNITS_PER_QUERY = 64;
 struct Ws {
     int32_t* ctrl;    // [0] queue pushes [2] queries to finish [5] 3p units pushed
     int32_t* qf;      // [B][QF]: list k at [2k, 2k+1) edge range; [6] bit k: list k staged,
-                      // [7] the draws of a query to finish
+                      // [7] the draws of a query to finish, [4] (where no third list
+                      // is) how many of them are non-answers and how many pending
     uint8_t* status;  // [B][neg_tries] ST_*
     int32_t* act[2];  // [0] queries to finish [1] by query: negatives selected so far (and from
                       // bit 16 on the finishing workgroups that are done with its first range)
@@ -1601,6 +1602,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         if (RootRels<QT>::mask >> k & 1) need |= sig_bit(rel[k]);
     int32_t acc = 0, base = 0, end = j_first, cnt = 0;
     bool deferred = false;
+    int32_t non_left = 0, pend_left = 0;   // states of the draws that are left
     int32_t steps = DEEP_STEPS;
     int32_t jsel = 0;     // draws [0, jsel) are selected
     bool to_stage = used > 0;
@@ -1761,9 +1763,15 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
         } else {
             deferred = deferred || any_left;
             if (deferred) {
-                for (int32_t i = lane; i < n; i += 64)
-                    sv[base + i] = L.non[i >> 5] >> (i & 31) & 1u ? ST_NON
-                                   : L.cand[i] < 0 ? ST_PEND : ST_ANS;
+                for (int32_t i0 = 0; i0 < n; i0 += 64) {
+                    const int32_t i = i0 + lane;
+                    const int32_t st = i >= n ? ST_ANS
+                                       : L.non[i >> 5] >> (i & 31) & 1u ? ST_NON
+                                       : L.cand[i] < 0 ? ST_PEND : ST_ANS;
+                    if (i < n) sv[base + i] = (uint8_t)st;
+                    non_left += __popcll(__ballot(st == ST_NON));
+                    pend_left += __popcll(__ballot(st == ST_PEND));
+                }
             } else {
                 if (!table) table_fill(tab, tb.tcap, out.negatives + (int64_t)b * p.n_neg, acc, lane);
                 table = tb.own;
@@ -1785,6 +1793,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
     } else if (deferred) {
         if (lane == 0) {
             qb[7] = pack_range(jsel, base);
+            if constexpr (Shape<QT>::nf < 3) qb[4] = pack_range(non_left, pend_left);
             ws.act[1][b] = acc;
             ws.act[0][atomicAdd(&ws.ctrl[2], 1)] = b;
         }
@@ -2290,7 +2299,7 @@ __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, sm
 {
     __shared__ WaveLds L;
     __shared__ uint16_t items[SMORE_MAX_NEG_TRIES];   // pending draws of the range
-    __shared__ int32_t n_items, count[2], next[2];
+    __shared__ int32_t n_items, count, next[2];
     extern __shared__ __align__(16) int32_t own_tab[];
     int32_t* tab = tb.own ? own_tab : (int32_t*)&L;
     const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), nw = blockDim.x >> 6;
@@ -2307,21 +2316,27 @@ __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, sm
         int32_t acc = uni(ws.act[1][b]) & 0xFFFF;
         int32_t shares = 1;
         if (per > 1) {
-            if (tid < 2) count[tid] = 0;
-            __syncthreads();
+            // all of a query's workgroups have to come to the same shares, whenever
+            // each of them starts: counts that none of them changes.  (The states
+            // do change: a workgroup that came late saw fewer pending ones, and
+            // with other shares the query was never finished.)
             int32_t non = 0, pend = 0;
-            for (int32_t j = j0 + 64 * w; j < j1; j += 64 * nw) {
-                const int32_t st = j + lane < j1 ? ws.status[(int64_t)b * p.neg_tries + j + lane] : ST_ANS;
-                non += __popcll(__ballot(st == ST_NON));
-                pend += __popcll(__ballot(st == ST_PEND));
+            if constexpr (QT == Q3P) {
+                // verdicts of earlier kernels: none is pending, none is changed here
+                if (tid == 0) count = 0;
+                __syncthreads();
+                for (int32_t j = j0 + 64 * w; j < j1; j += 64 * nw) {
+                    const int32_t st = j + lane < j1 ? ws.status[(int64_t)b * p.neg_tries + j + lane] : ST_ANS;
+                    non += __popcll(__ballot(st == ST_NON));
+                }
+                if (lane == 0) atomicAdd(&count, non);
+                __syncthreads();
+                non = uni(count);
+            } else {
+                const int32_t left = uni(ws.qf[(int64_t)b * QF + 4]);
+                non = range_lo(left);
+                pend = range_hi(left);
             }
-            if (lane == 0) {
-                atomicAdd(&count[0], non);
-                atomicAdd(&count[1], pend);
-            }
-            __syncthreads();
-            non = uni(count[0]);
-            pend = uni(count[1]);
             j1 = likely_end(p, g.V, mid, acc + non, mid - j0 - non - pend, pend);
             shares = min(per, max(1, (pend + j1 - mid + nw - 1) / nw));   // a wavefront has work in each
         }

@@ -6,7 +6,7 @@ import pytest
 
 import kgsynth
 import paper_2110_14890_amd as sm
-from gpu_common import assert_same, gpu_sample, graph_pair, progress, require_gpu
+from gpu_common import assert_same, gpu_sample, graph_pair, progress, require_gpu, to_numpy
 from test_gpu_parity import hub_graph_3p
 
 pytestmark = pytest.mark.gpu
@@ -83,3 +83,26 @@ def test_one_query_is_shared_by_workgroups(qt):
     one, many = call_ms(g, qt, 4, 1000), call_ms(g, qt, 256, 1000)
     progress(f"{qt}: 4 queries {one:.2f} ms, 256 queries {many:.2f} ms")
     assert one < 0.6 * many
+
+
+# Beside a call that holds the GPU the workgroups that share a query start at
+# different times, some after others have settled draws: they all have to come
+# to the same shares of it.
+@pytest.mark.parametrize("qt", LONG)
+def test_shared_queries_beside_a_call_that_fills_the_gpu(qt):
+    import torch
+    rng = np.random.default_rng(43)
+    g, og = graph_pair(kgsynth.random_tiny(rng, 2000, 3, 300000), 2000, 3)
+    busy, here = torch.cuda.Stream(), torch.cuda.Stream()
+    big = sm.alloc_outputs(16384, 512)
+    big_ws, ws = sm.Workspace(), sm.Workspace()
+    outs = [sm.alloc_outputs(16, 500) for _ in range(8)]
+    torch.cuda.synchronize()
+    for k, out in enumerate(outs):
+        sm.sample_into(g, sm.query_preset("1p"), sm.make_args(16384, 512, seed=1), big, stream=busy, workspace=big_ws)
+        sm.sample_into(g, sm.query_preset(qt), sm.make_args(16, 500, seed=9, query_offset=16 * k), out,
+                       stream=here, workspace=ws)
+    torch.cuda.synchronize()
+    for k, out in enumerate(outs):
+        ref = og.sample(qt, 16, 500, seed=9, query_offset=16 * k, neg_tries=2000)
+        assert_same(to_numpy(out), ref, what=f"{qt} call {k}")
