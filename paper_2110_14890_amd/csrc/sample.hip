@@ -2346,8 +2346,13 @@ __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, sm
         T tl;
         for (;;) {
             // states of the draws [mid, j1) and verdicts of the pending ones of
-            // [j0, j1): runs of `each` draws, dealt over shares and wavefronts
-            const int32_t each = shares > 1 ? min(64, max(1, (j1 - j0) / (shares * nw))) : 64;
+            // [j0, j1): runs of `each` draws, dealt over shares and wavefronts.  A
+            // query that is short of a few draws has them taken by all wavefronts, a
+            // few each, since a step lasts as long as the longest lists of its draws
+            // (256 queries x 200 of 2p on a dense graph: 64 draws a wavefront in
+            // ranges of at least 64 per wavefront 285 us, this way 182).
+            const int32_t each = shares > 1 ? min(64, max(1, (j1 - j0) / (shares * nw)))
+                                            : min(64, max(1, (j1 - j0 + nw - 1) / nw));
             for (int32_t r = share + shares * w; mid < j1 && j0 + r * each < j1; r += shares * nw) {
                 const int32_t ja = max(j0 + r * each, mid), jb = min(j0 + (r + 1) * each, j1);
                 if (ja < jb) finish_draws<QT>(g, p, L, q, b, ja, jb, sv, lane, tl);
@@ -2399,10 +2404,7 @@ __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, sm
                 }
                 if (lane == 0) {
                     next[0] = j0;
-                    // where the GPU is not full, a range that the workgroup's wavefronts
-                    // take at once costs no more than a shorter one
-                    const int32_t least = 2 * n <= (int32_t)gridDim.x ? j0 + 64 * nw : j0;
-                    next[1] = acc < p.n_neg ? min(max(next_round_end(p, j0, acc), least), p.neg_tries) : j0;
+                    next[1] = acc < p.n_neg ? next_round_end(p, j0, acc) : j0;
                 }
             }
             __syncthreads();
