@@ -66,11 +66,14 @@ def sample_hip_sha():
 def first_round_draws(n_neg, neg_tries, batch=4096):
     """Candidate draws of the first round of smore_sample_negatives: n_neg
     plus a margin of n_neg / 32 + 8, at most neg_tries; a batch under 4,096
-    fills its last 64 draws up."""
+    fills its last 64 draws up, by at least 16, but not past a window of 576."""
     e = min(n_neg + n_neg // 32 + 8, neg_tries)
     if batch >= 4096:
         return e
-    return max(e, min((e + 16 + 63) // 64 * 64, neg_tries, max(e, neg_tries - e)))
+    full = (e + 16 + 63) // 64 * 64
+    if e <= 576:
+        full = min(full, 576)
+    return max(e, min(full, neg_tries, max(e, neg_tries - e)))
 
 
 def oracle_lines(og, cfg, types, neg_tries, threads):

@@ -641,6 +641,7 @@ __device__ __forceinline__ int32_t candidate(const SampleParams& p, int32_t V, i
 // needs at the acceptance rate it has had so far, with a margin
 // (next_round_end).  Rounds are a scheduling detail: a query's negatives are
 // its first n_neg accepted draws in draw order whatever the rounds were.
+constexpr int WIN = 576;   // draws of a window
 inline int32_t first_margin(const SampleParams& p)
 {
     const int64_t e = (int64_t)p.n_neg + p.n_neg / 32 + 8;
@@ -656,14 +657,18 @@ inline int32_t max_round_len(const SampleParams& p)
 
 // A batch under 4,096 queries does not fill the GPU's wavefronts, and its
 // time is that of its slowest ones: there the first round fills its last 64
-// draws up (they cost no further step), so that fewer queries need another
-// chain of dependent reads.  Above, the draws themselves are the cost.  The
-// queue has to hold the round.
+// draws up, and takes 64 more where fewer than 16 would be left to add, so
+// that fewer queries need another chain of dependent reads.  Above, the draws
+// themselves are the cost.  A round that fits one window stays in it (n_neg
+// 537 to 551: with 640 draws the selection table is one of its own, which
+// leaves a CU nine wavefronts in place of 16).  The queue has to hold the round.
 inline int32_t first_round(const SampleParams& p)
 {
     const int32_t e = first_margin(p);
     if (p.batch >= 4096) return e;
-    return max(e, min((e + 16 + 63) / 64 * 64, min(p.neg_tries, max_round_len(p))));
+    int32_t full = (e + 16 + 63) / 64 * 64;
+    if (e <= WIN) full = min(full, WIN);
+    return max(e, min(full, min(p.neg_tries, max_round_len(p))));
 }
 
 // End of the next range of a query that has `kept` accepted draws among its
@@ -748,7 +753,6 @@ __device__ __forceinline__ void flush_tally(T& tl, int64_t* stats, int32_t b, in
 // so one LDS read settles nearly every lookup, and only the others bisect
 // the list.  The sizes keep it at 10,240 bytes, eight of the 1,280-byte units
 // that LDS is given out in: 16 wavefronts per CU, as their registers allow.
-constexpr int WIN = 576;
 constexpr int DPW = WIN / 64;
 constexpr int WORDS = WIN / 32;
 constexpr int DEEPQ = 192;       // deep items held before a pass over 64 of them: 63 + one step of 128

@@ -22,6 +22,16 @@ def test_traffic_sums_the_kernels_timed_as_one_unit():
     assert bench.traffic_for("no_such_workload", "k_heavy<3p> r0") is None
 
 
+def test_first_round_draws():
+    assert bench.first_round_draws(512, 2048, 4096) == 536
+    assert bench.first_round_draws(128, 512, 512) == 192
+    assert bench.first_round_draws(54, 216, 512) == 128          # 63 and a margin of 16
+    assert bench.first_round_draws(536, 2144, 64) == 576
+    assert bench.first_round_draws(551, 2204, 64) == 576         # 576 as they are: one window
+    assert bench.first_round_draws(552, 2208, 64) == 640
+    assert bench.first_round_draws(551, 1000, 64) == 576
+
+
 def test_traffic_is_null_for_other_sources(monkeypatch):
     monkeypatch.setattr(bench, "sample_hip_sha", lambda: "0000000000000000")
     assert bench.traffic_for("freebase", "k_candidates<3p> r0") is None
