@@ -21,10 +21,13 @@ def _gpu():
     require_gpu()
 
 
-# n_neg 550 is the longest row whose first draws are one window of 576, with
-# the selection table over the staged lists; 551 the shortest with its own
+# n_neg 551 is the longest row whose first draws (n_neg + n_neg / 32 + 8) are
+# one window of 576, with the selection table over the staged lists; 552 the
+# shortest with its own, and with a second window of one draw where the budget
+# or the batch leaves its 577 as they are
 @pytest.mark.parametrize("n_neg,neg_tries", [(1, 2), (56, 64), (57, 200), (549, 576), (550, 1000),
-                                             (551, 1000), (560, 4096), (1100, 1200), (4096, 4096)])
+                                             (551, 1000), (552, 1000), (552, 577), (536, 2144), (537, 2148),
+                                             (551, 2204), (560, 4096), (1100, 1200), (4096, 4096)])
 def test_rows_around_the_window(n_neg, neg_tries):
     rng = np.random.default_rng(21)
     tr = kgsynth.random_tiny(rng, 6000, 4, 90000)
@@ -33,6 +36,18 @@ def test_rows_around_the_window(n_neg, neg_tries):
         progress(f"window {qt} n_neg {n_neg}")
         got = gpu_sample(g, qt, 65, n_neg, seed=2, neg_tries=neg_tries)
         ref = og.sample(qt, 65, n_neg, seed=2, neg_tries=neg_tries)
+        assert_same(got, ref, what=f"{qt} n_neg {n_neg}")
+
+
+@pytest.mark.parametrize("n_neg", [551, 552])
+def test_rows_around_the_window_of_a_full_batch(n_neg):
+    rng = np.random.default_rng(25)
+    tr = kgsynth.random_tiny(rng, 6000, 4, 90000)
+    g, og = graph_pair(tr, 6000, 4, False)
+    for qt in ("1p", "ip"):
+        progress(f"full batch {qt} n_neg {n_neg}")
+        got = gpu_sample(g, qt, 4096, n_neg, seed=2)
+        ref = og.sample(qt, 4096, n_neg, seed=2)
         assert_same(got, ref, what=f"{qt} n_neg {n_neg}")
 
 
