@@ -41,6 +41,24 @@ def test_verify_parity_random_candidates(qt):
         assert nv[7] == -1
 
 
+# backward lists of one and two entities, with one and two in-neighbours each
+# or a few more, on both sides of the lists a lane takes itself; forward lists
+# shorter and longer than them
+@pytest.mark.parametrize("V,R,n_edges", [(1000, 20, 10_100), (1000, 40, 6000), (400, 2, 700), (60, 1, 200)])
+def test_verify_short_lists_3p(V, R, n_edges):
+    require_gpu()
+    rng = np.random.default_rng(32)
+    g, og = graph_pair(kgsynth.random_tiny(rng, V, R, n_edges), V, R, True)
+    q = og.sample("3p", 600, 0, seed=3, neg_tries=0)
+    for n in (1, 64, 700):
+        progress(f"short lists V {V} n {n}")
+        cand = rng.integers(-1, V + 1, size=(600, n)).astype(np.int32)
+        cand[:, 0] = q["positive"]
+        mask, nv = gpu_verify(g, "3p", q["anchors"], q["relations"], cand)
+        ref = og.verify("3p", q["anchors"], q["relations"], cand)
+        assert np.array_equal(mask, ref["mask"]) and np.array_equal(nv, ref["n_valid"]), f"V {V} n {n}"
+
+
 def test_evaluation_on_nested_graphs():
     """G_train within G_valid within G_test (90 / 5 / 5 % of the triples):
     test queries with 1,000 filtered negatives from G_test; their positives
