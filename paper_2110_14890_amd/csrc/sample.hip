@@ -66,8 +66,6 @@ enum : int32_t { ST_NON = 0, ST_ANS = 1, ST_PEND = 3, ST_DEEP = 4 };
 struct NoTally {
     static constexpr bool on = false;
     __device__ __forceinline__ void read(const void*, int32_t) {}
-    __device__ __forceinline__ void bytes_only(int64_t) {}
-    __device__ __forceinline__ void add(const NoTally&) {}
 };
 struct Tally {
     static constexpr bool on = true;
@@ -79,8 +77,6 @@ struct Tally {
         b += (uint64_t)nbytes;
         l += ((a + nbytes - 1) >> 6) - (a >> 6) + 1;
     }
-    __device__ __forceinline__ void bytes_only(int64_t n) { b += (uint64_t)n; }
-    __device__ __forceinline__ void add(const Tally& o) { b += o.b, l += o.l; }
 };
 
 // Edges [x, y) of v under r when v's node-pointer pair (n0, n1) is known.
@@ -239,40 +235,9 @@ __device__ __forceinline__ void search4(const int32_t* B, int32_t nb, const int3
 }
 
 // search4 with a target list per key (lists of different lengths; the loop
-// runs until every key of the lane is settled).
-template <class T>
-__device__ __forceinline__ void search4v(const int32_t* const* B, const int32_t* nb, const int32_t* x,
-                                         const bool* count, bool* found, T& tl)
-{
-    int32_t base[4] = {0, 0, 0, 0}, n[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) n[k] = nb[k];
-    for (;;) {
-        bool more = false;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (n[k] > 1) {
-                const int32_t half = n[k] >> 1;
-                if (count[k]) tl.read(B[k] + base[k] + half, 4);
-                base[k] = B[k][base[k] + half] <= x[k] ? base[k] + half : base[k];
-                n[k] -= half;
-                more |= n[k] > 1;
-            }
-        }
-        if (!more) break;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        found[k] = false;
-        if (nb[k] > 0) {
-            if (count[k]) tl.read(B[k] + base[k], 4);
-            found[k] = B[k][base[k]] == x[k];
-        }
-    }
-}
-
-// search4v with three probes per step where four or more entries remain
-// (a quaternary search: fewer dependent reads, more reads in all).
+// runs until every key of the lane is settled), and three probes per step
+// where four or more entries remain (a quaternary search: fewer dependent
+// reads, more reads in all).
 template <class T>
 __device__ __forceinline__ void search4q(const int32_t* const* B, const int32_t* nb, const int32_t* x,
                                          const bool* count, bool* found, T& tl)
@@ -1181,75 +1146,6 @@ __device__ bool heavy_test(const GraphView& g, const FSet* F, const int32_t* rel
     if (QT == QUP)
         return wave_meet(S, ns, true, F[0].p, F[0].n, false, lane, tl) ||
                wave_meet(S, ns, true, F[1].p, F[1].n, false, lane, tl);
-    if (QT == Q3P) {
-        // second backward step for 64 entities y of R_r2(c) at a time; every
-        // pair (y, key) with key from the shorter of R_r1(y) and F0 is one
-        // search in the longer, and all pairs of the 64 y's are spread over
-        // the wavefront, four per lane, so they share one search chain
-        for (int32_t k = 0; k < ns; k += 64) {
-            if (lane == 0) tl.read(S + k, 4 * min(64, ns - k));
-            int2 s2 = make_int2(0, 0);
-            if (k + lane < ns) {
-                // y without an in-edge under r1's signature class has none under r1
-                const int32_t y = S[k + lane];
-                tl.read(g.sig + y, 1);
-                if (g.sig[y] & sig_bit(rel[1])) s2 = group_range(g.rev, y, rel[1], tl);
-            }
-            const int32_t len = s2.y - s2.x;
-            const bool keys_in_list = len <= F[0].n;       // search R_r1(y) entries in F0
-            const int32_t npair = len > 0 ? min(len, F[0].n) : 0;
-            int32_t incl = npair;                           // inclusive prefix over the lanes
-            for (int d = 1; d < 64; d <<= 1) {
-                const int32_t v = __shfl_up(incl, d);
-                if (lane >= d) incl += v;
-            }
-            const int32_t total = uni(__shfl(incl, 63));
-            const int32_t excl = incl - npair;
-            for (int32_t p0 = 0; p0 < total; p0 += 256) {
-                const int32_t* Bk[4];
-                int32_t nbk[4], x[4];
-                bool cnt[4], found[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int32_t pi = p0 + 64 * u + lane;
-                    const int32_t pq = pi < total ? pi : total - 1;
-                    // owner lane of pair pq: the highest lane whose exclusive
-                    // prefix is <= pq (binary lifting, every lane active)
-                    int32_t lo = 0;
-#pragma unroll
-                    for (int step = 32; step >= 1; step >>= 1) {
-                        const int32_t cand = lo + step;
-                        const int32_t ev = __shfl(excl, cand > 63 ? 63 : cand);
-                        if (cand <= 63 && ev <= pq) lo = cand;
-                    }
-                    const int32_t off = pq - __shfl(excl, lo);
-                    const int32_t lx = __shfl(s2.x, lo);
-                    const int32_t ln = __shfl(len, lo);
-                    const int32_t kil = __shfl((int32_t)keys_in_list, lo);
-                    Bk[u] = F[0].p;
-                    nbk[u] = 0;
-                    x[u] = -1;
-                    cnt[u] = false;
-                    if (pi < total) {
-                        if (kil) {
-                            x[u] = g.rev.nbr[lx + off];
-                            tl.read(g.rev.nbr + lx + off, 4);
-                            Bk[u] = F[0].p;
-                            nbk[u] = F[0].n;
-                        } else {
-                            x[u] = F[0].p[off];
-                            Bk[u] = g.rev.nbr + lx;
-                            nbk[u] = ln;
-                            cnt[u] = true;
-                        }
-                    }
-                }
-                search4v(Bk, nbk, x, cnt, found, tl);
-                if (__ballot(found[0] || found[1] || found[2] || found[3])) return true;
-            }
-        }
-        return false;
-    }
     return false;
 }
 
@@ -1902,24 +1798,25 @@ __device__ __forceinline__ void put_verdict(const SampleParams& p, const smore_s
     }
 }
 
-// Persistent wavefronts draining the heavy queue.  Wavefront w takes items
+// Persistent wavefronts draining the heavy queue of given candidates (a
+// sampling call's long lists are the finishing kernel's).  Wavefront w takes items
 // w, w + nwaves, ... (no shared counter to contend on).  It looks up its
 // next 64 items at once, one per lane: the queue entry, the candidate, the
 // query's relations and cached lists, and the candidate's backward list,
 // so those dependent reads overlap instead of preceding each test in turn.
-template <int QT, class T>
+template <int QT>
 __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p, smore_sample_out out,
-                                                    Ws ws, int64_t* stats, uint32_t* mask)
+                                                    Ws ws, uint32_t* mask)
 {
     constexpr int NF = Shape<QT>::nf;
     const int lane = threadIdx.x & 63;
     const int32_t total = uni(ws.ctrl[0]);
     const int32_t nwaves = gridDim.x * (HEAVY_WG / 64);
     const int32_t w0 = uni(blockIdx.x * (HEAVY_WG / 64) + (threadIdx.x >> 6));
-    T tl;
+    NoTally none;
     for (int64_t base = w0; base < total; base += 64 * (int64_t)nwaves) {
         const int64_t mine = base + (int64_t)lane * nwaves;
-        int32_t mb = 0, mc = 0, mj = 0;
+        int32_t mb = 0, mj = 0;
         int32_t mrel[3] = {0, 0, 0}, mf[2 * NF];
         int2 ms = make_int2(0, 0);
 #pragma unroll
@@ -1928,13 +1825,12 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p,
             const int2 it = ws.queue[mine];
             mb = it.x;
             mj = it.y;
-            mc = candidate(p, g.V, it.x, it.y);
 #pragma unroll
             for (int k = 0; k < 3; ++k) mrel[k] = out.relations[3 * (int64_t)mb + k];
             const int32_t* qb = ws.qf + (int64_t)mb * QF;
 #pragma unroll
             for (int f = 0; f < 2 * NF; ++f) mf[f] = qb[f];
-            ms = group_range(g.rev, mc, chain_r1<QT> ? mrel[1] : mrel[2]);
+            ms = group_range(g.rev, candidate(p, g.V, it.x, it.y), chain_r1<QT> ? mrel[1] : mrel[2]);
         }
         const int32_t n = uni((int32_t)min((int64_t)64, (total - base + nwaves - 1) / nwaves));
         for (int k = 0; k < n; ++k) {
@@ -1952,16 +1848,9 @@ __global__ __launch_bounds__(HEAVY_WG) void k_heavy(GraphView g, SampleParams p,
                     F[f] = FSet{nullptr, 0};
                 }
             }
-            if constexpr (T::on) {
-                // the candidate's lookup, charged once to its query
-                T one;
-                (void)group_range(g.rev, readlane(mc, k), chain_r1<QT> ? rel[1] : rel[2], one);
-                if (lane == 0) tl = one;
-            }
             const int2 s = make_int2(readlane(ms.x, k), readlane(ms.y, k));
-            const bool ans = heavy_test<QT>(g, F, rel, s, lane, tl);
+            const bool ans = heavy_test<QT>(g, F, rel, s, lane, none);
             if (lane == 0) put_verdict(p, out, ws, mask, b, readlane(mj, k), ans);
-            flush_tally(tl, stats, b, lane, 2);
         }
     }
 }
@@ -2575,7 +2464,7 @@ int launch_long_lists(const GraphView& gv, const SampleParams& p, const smore_sa
         if ((rc = check_launch(err))) return rc;
         k_units3<T><<<grid, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, mask);
     } else {
-        k_heavy<QT, T><<<PERSIST_BLOCKS, HEAVY_WG, 0, st>>>(gv, p, out, ws, stats, mask);
+        k_heavy<QT><<<PERSIST_BLOCKS, HEAVY_WG, 0, st>>>(gv, p, out, ws, mask);
     }
     return check_launch(err);
 }
