@@ -713,7 +713,7 @@ __device__ __forceinline__ void flush_tally(T& tl, int64_t* stats, int32_t b, in
 }
 
 // LDS of one wavefront of the candidate kernels.  Staged lists keep their
-// order in `stage` and have a hashed bit set each in `bits` (split evenly
+// order in `stage` and have a hashed bit set each in bits() (split evenly
 // between the shape's lists): a value whose bit is clear is not in the list,
 // so one LDS read settles nearly every lookup, and only the others bisect
 // the list.  The sizes keep it at 10,240 bytes, eight of the 1,280-byte units
@@ -723,14 +723,15 @@ constexpr int WORDS = WIN / 32;
 constexpr int DEEPQ = 192;       // deep items held before a pass over 64 of them: 63 + one step of 128
 constexpr int BIT_WORDS = 256;
 struct alignas(16) WaveLds {
-    int32_t stage[STAGE];
-    uint32_t bits[BIT_WORDS];
+    int32_t stage[STAGE + BIT_WORDS];   // the lists, their bits after them; or the selection table
     int32_t cand[WIN];      // the window's candidates (complemented: left to the long-list kernels)
     int32_t ds[DEEPQ];      // deep items: start of the backward list
     uint16_t dl[DEEPQ];     //             its length, at most 65,535
     uint16_t dj[DEEPQ];     //             index in the window
     uint16_t sj[WIN];       // survivors of the first test: index in the window
     uint32_t non[WORDS];    // bit i: candidate i is a non-answer
+    __device__ __forceinline__ uint32_t* bits() { return (uint32_t*)stage + STAGE; }
+    __device__ __forceinline__ const uint32_t* bits() const { return (const uint32_t*)stage + STAGE; }
 };
 
 static_assert(sizeof(WaveLds) <= 10240, "LDS of a wavefront");
@@ -750,7 +751,7 @@ template <int QT> __device__ __forceinline__ uint32_t bit_slot(int f, int32_t x)
 template <int QT> __device__ __forceinline__ bool maybe_in(const WaveLds& L, int f, int32_t x)
 {
     const uint32_t h = bit_slot<QT>(f, x);
-    return L.bits[h >> 5] >> (h & 31) & 1u;
+    return L.bits()[h >> 5] >> (h & 31) & 1u;
 }
 
 // Is x in the staged list F?
@@ -1509,7 +1510,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
     }
     // copy of the staged lists into the wave's LDS slice, with their bits
     auto stage_lists = [&]() {
-        for (int k = lane; k < BIT_WORDS; k += 64) L.bits[k] = 0;
+        for (int k = lane; k < BIT_WORDS; k += 64) L.bits()[k] = 0;
         wave_sync();
 #pragma unroll
         for (int f = 0; f < Shape<QT>::nf; ++f) {
@@ -1524,7 +1525,7 @@ __device__ __forceinline__ void query_draws(const GraphView& g, const SamplePara
                     if (k0 + 64 * u >= F[f].n) break;
                     const uint32_t h = bit_slot<QT>(f, x[u]);
                     L.stage[F[f].off + k0 + 64 * u] = x[u];
-                    atomicOr(&L.bits[h >> 5], 1u << (h & 31));
+                    atomicOr(&L.bits()[h >> 5], 1u << (h & 31));
                 }
             }
         }
@@ -2243,7 +2244,7 @@ __global__ __launch_bounds__(1024) void k_finish(GraphView g, SampleParams p, sm
     __shared__ uint16_t items[SMORE_MAX_NEG_TRIES];   // pending draws of the range
     __shared__ int32_t n_items, count, next[2];
     extern __shared__ __align__(16) int32_t own_tab[];
-    int32_t* tab = tb.own ? own_tab : (int32_t*)&L;
+    int32_t* tab = tb.own ? own_tab : L.stage;
     const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), nw = blockDim.x >> 6;
     const int32_t n = uni(ws.ctrl[2]);
     // workgroups per query: one where the call fills the GPU
