@@ -21,9 +21,10 @@ Roofline.  The algorithmic bytes of a launch come from the oracle, not from
 the kernels: oracle_verify_lines counts, per query, the distinct 64-byte
 lines of the device layout a bidirectional check under the strict node cut
 reads for the first round's candidate draws (forward caching, each
-candidate's node entries and group search, backward lists), split into the
-part a first verification pass makes and the part below long lists or
-forward sets too large to stage.  `roofline` is for the longest kernel of
+candidate's node entries and group search, backward lists).  Which lists a
+candidate wavefront leaves to another kernel depends on the steps it has
+taken, so a shape's lines are divided between its two kernels in the
+proportion of their own read tallies.  `roofline` is for the longest kernel of
 the step by event time; `kernels` gives every candidate and long-list
 kernel beside it with the same accounting, the kernels' own read tally and,
 when the committed counter summary matches the current sources, the HBM
@@ -81,9 +82,9 @@ def oracle_lines(og, cfg, types, neg_tries, threads):
     the oracle: positives of the benchmark's first batch (query ids
     0 .. batch-1) by the oracle's own reverse sampling, then
     oracle_verify_lines under the strict node cut (oracle/cuts.py) for the
-    first round's draws.  Lines x 64 B; part 0 = the first verification
-    pass (the candidate kernel's share), part 1 = long lists and unstaged
-    forward sets (the long-list kernel's share)."""
+    first round's draws.  Lines x 64 B; part 0 = forward caching, lookups
+    and lists of at most 8 entries, part 1 = longer lists and forward sets
+    over 1,024 entries, total = the distinct lines of both."""
     from oracle import cuts
 
     res = {}
@@ -104,6 +105,14 @@ def oracle_lines(og, cfg, types, neg_tries, threads):
                    "seconds": round(time.time() - t, 2)}
         log(f"oracle lines {qt}: {res[qt]}")
     return res
+
+
+def kernel_share(total, cand_lines, heavy_lines, kind):
+    """A shape's algorithmic bytes that one of its kernels is charged: in
+    proportion to the lines that the candidate kernel and the kernel that
+    intersects long lists count themselves."""
+    both = cand_lines + heavy_lines
+    return total * (cand_lines if kind == "cand" else heavy_lines) // both if both else 0
 
 
 def workload_name(cfg, types):
@@ -673,8 +682,8 @@ def main():
     outs = outs_p[0]
 
     # untimed accounting pass on the first batch: graph bytes / 64-byte lines
-    # the verification kernels read by their own tally, [0:2] in the
-    # candidate kernel, [2:4] in the long-list kernel
+    # the verification kernels read by their own tally, [0:2] by the
+    # wavefronts that take the draws, [2:4] in intersections of longer lists
     acct = {}
     first = step_args(0)
     for qt in types:
@@ -945,7 +954,7 @@ def main():
         tally = acct[qt]["cand_lines" if kind == "cand" else "heavy_lines"] * 64
         algo = None
         if lines:
-            algo = lines[qt]["part0_bytes" if kind == "cand" else "part1_bytes"]
+            algo = kernel_share(lines[qt]["total_bytes"], acct[qt]["cand_lines"], acct[qt]["heavy_lines"], kind)
         traffic = traffic_for(cfg.name, name)
         gbps = lambda nbytes: nbytes / (ms / 1e3) / 1e9 if nbytes is not None and ms > 0 else None
         achieved = gbps(algo)
@@ -974,8 +983,8 @@ def main():
         "achieved = algorithmic bytes / avg_launch_ms; algorithmic bytes = 64 x the distinct 64-byte "
         "lines per query that the oracle's bidirectional check under the strict node cut reads for "
         "the first round's candidate draws (node entries, group search, lists of the device layout), "
-        "summed over the batch; the candidate kernel is charged the first verification pass, the "
-        "long-list kernel the lists longer than 8 entries and forward sets over 1,024 entries; "
+        "summed over the batch, and divided between the shape's candidate kernel and the kernel "
+        "that intersects the lists it leaves in the proportion of their own line tallies; "
         "kernel_tally is the kernel's own count of the lines of each read it makes; traffic is "
         "rocprofv3 FETCH_SIZE + WRITE_SIZE scaled by a plain copy")
 

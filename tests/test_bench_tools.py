@@ -22,6 +22,13 @@ def test_traffic_sums_the_kernels_timed_as_one_unit():
     assert bench.traffic_for("no_such_workload", "k_heavy<3p> r0") is None
 
 
+def test_kernel_shares_make_up_the_shape():
+    for total, cand, heavy in [(1000, 3, 1), (64 * 58_313, 9_000_000, 120_000), (640, 0, 5), (0, 4, 4)]:
+        a, b = (bench.kernel_share(total, cand, heavy, k) for k in ("cand", "heavy"))
+        assert 0 <= total - a - b <= 1 and a * heavy <= total * cand
+    assert bench.kernel_share(640, 7, 0, "heavy") == 0 and bench.kernel_share(640, 0, 0, "cand") == 0
+
+
 def test_first_round_draws():
     assert bench.first_round_draws(512, 2048, 4096) == 536
     assert bench.first_round_draws(128, 512, 512) == 192
