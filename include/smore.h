@@ -149,9 +149,9 @@ int smore_query_preset(const char *name, smore_query_dag *out);
 int smore_plan(const smore_query_dag *dag, int32_t tie_break, int32_t *cut_nodes, int32_t *n_cut);
 
 /* Bytes of device workspace smore_sample / smore_sample_negatives need for
-   these arguments (it grows with batch * neg_tries: per-draw candidate ids
-   and states, the queue of long intersections, the lists of queries still
-   short of n_neg).  The caller allocates it; its contents need no
+   these arguments (it grows with batch * neg_tries: per-draw states, the
+   queues of long intersections, the list ranges of each query and the
+   queries still short of n_neg; the same for every shape).  The caller allocates it; its contents need no
    initialisation and are scratch after the call.  Calls that may overlap on
    the device must not share a workspace.  A call with n_neg = 0 draws no
    candidates and needs no workspace (NULL and 0 are accepted). */

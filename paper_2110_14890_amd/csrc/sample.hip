@@ -415,9 +415,8 @@ __device__ bool neg_member(const GraphView& g, int steps, int32_t a, int32_t r0,
 // Attempts of one query run PA at a time, on PA neighbouring lanes (lane l
 // of the group takes attempts l, l + PA, ...): the lowest successful
 // attempt of a group step is the first successful attempt overall, so the
-// result is that of trying them one after the other.  Four lanes per query,
-// eight for plans with a complemented operand, whose attempts are rejected
-// more often.
+// result is that of trying them one after the other.  positive_lanes chooses
+// PA.
 
 // One attempt t of query q: true and the grounded registers when accepted.
 __device__ __forceinline__ bool pos_attempt(const GraphView& g, const WalkProgram& wp,
@@ -549,10 +548,10 @@ template <> struct RootLists<Q2IN> { static constexpr int mask = 1, any = 0; };
 template <> struct RootLists<Q3IN> { static constexpr int mask = 3, any = 0; };
 template <> struct RootLists<QPNI> { static constexpr int mask = 2, any = 0; };
 
-// The candidate kernel runs one wavefront per workgroup, and its first pass
-// one query per workgroup: queries differ widely in cost, and the hardware
-// dispatcher hands each freed slot the next query, where a fixed share per
-// wavefront leaves the kernel waiting on its slowest shares.
+// The candidate kernel runs one wavefront and one query per workgroup: queries
+// differ widely in cost, and the hardware dispatcher hands each freed slot the
+// next query, where a fixed share per wavefront leaves the kernel waiting on
+// its slowest shares.
 constexpr int CWG = 64;
 constexpr int HEAVY_WG = 256;    // threads of the heavy-queue workgroups
 constexpr int QF = 8;            // int32 per query in the per-query block
@@ -2416,8 +2415,9 @@ inline int check_launch(const char** err)
     return SMORE_OK;
 }
 
-// One-shot event pairs of the next negatives call, one per kernel kind
-// (0 candidate kernel, 1 long-list kernel, 2 selection), each independent.
+// One-shot event pairs of the next negatives call, each independent: around
+// the candidate kernel (0), the long-list kernels (1: 3p's two, of the other
+// shapes the finishing kernel) and the finishing kernel (2).
 struct ProfileArm {
     hipEvent_t start = nullptr, stop = nullptr;
 };
@@ -2439,9 +2439,10 @@ inline void prof_mark(int which, bool after, hipStream_t st)
 // 16, since a call of few queries would otherwise last as long as one
 // wavefront takes for all draws and lists of the worst query (16 queries x
 // 1,000 negatives on a graph of 2,000 entities and 300,000 triples, where most
-// candidates are answers: one wavefront for the draws 32.3 ms for 3p and 3.7
-// for 2p, sixteen 1.5 and 0.6).  3p leaves it no lists of the first draws:
-// calls that fill the GPU run one (Freebase-shaped step 598 us, with four 612).
+// candidates are answers: one wavefront for the draws 32.1 ms for 3p and 3.7
+// for 2p, sixteen, and a query's draws dealt over several workgroups, 0.30 and
+// 0.20).  3p leaves it no lists of the first draws: calls that fill the GPU
+// run one (Freebase-shaped step 598 us, with four 612).
 template <int QT>
 inline int finish_waves(const SampleParams& p)
 {
