@@ -2693,7 +2693,7 @@ GraphView view_of(const smore_graph* g)
     gv.has_in = g->has_in;
     gv.has_in4 = g->has_in4;
     gv.sig = g->sig;
-    gv.first_test = g->V <= (1 << 22) ? TEST_SIG : g->V <= (1 << 24) ? TEST_MASK : TEST_MASK4;
+    gv.first_test = g->V <= (1 << 22) ? TEST_SIG : g->V <= (1 << 26) ? TEST_MASK : TEST_MASK4;
     gv.V = g->V;
     gv.n_active = (int32_t)g->n_active;
     return gv;

@@ -21,9 +21,13 @@ struct DirView {
 };
 
 // First test of a draw: the in-relation signatures while they fit an XCD's
-// L2 (4 MiB: V up to 2^22), else the in-edge mask while it does (V / 8 bytes,
-// V up to 2^24: half the L2), else the coarse mask; after a mask, the
-// signatures of the draws it passes.
+// L2 (4 MiB: V up to 2^22), else the in-edge mask (V / 8 bytes) up to V =
+// 2^26, else the coarse mask (a quarter of it, which passes more draws); after
+// a mask, the signatures of the draws it passes.  2p, 8,192 queries x 512, four
+// edges per entity, us with the signatures / the mask / the coarse mask:
+// V = 2.5M 90 / 94 / 96, 2^22 125 / 128 / 131, 6M 114 / 112 / 121, 2^24
+// 137 / 112 / 130, 2^25 142 / 115 / 135, 60M 153 / 132 / 139, 86M 158 / 145 /
+// 140; ip and a step of 3p, ip and pi change sides at the same sizes.
 enum { TEST_SIG = 0, TEST_MASK = 1, TEST_MASK4 = 2 };
 
 struct GraphView {

@@ -97,8 +97,8 @@ def test_attempt_lanes(qt, batch, max_fanout):
 
 
 # the first test of a draw reads the signatures up to 2^22 entities, the
-# in-edge mask up to 2^24, the coarse mask above
-@pytest.mark.parametrize("V", [1 << 22, (1 << 22) + 1, 1 << 24, (1 << 24) + 1])
+# in-edge mask up to 2^26, the coarse mask above
+@pytest.mark.parametrize("V", [1 << 22, (1 << 22) + 1, 1 << 24, (1 << 24) + 1, 1 << 26, (1 << 26) + 1])
 def test_first_test_by_graph_size(V):
     rng = np.random.default_rng(24)
     ents = rng.choice(V, 60_000, replace=False).astype(np.int32)
