@@ -24,7 +24,8 @@ reads for the first round's candidate draws (forward caching, each
 candidate's node entries and group search, backward lists).  Which lists a
 candidate wavefront leaves to another kernel depends on the steps it has
 taken, so a shape's lines are divided between its two kernels in the
-proportion of their own read tallies.  `roofline` is for the longest kernel of
+proportion of the HBM bytes that they move (without a counter summary of the
+current sources, of their own read tallies).  `roofline` is for the longest kernel of
 the step by event time; `kernels` gives every candidate and long-list
 kernel beside it with the same accounting, the kernels' own read tally and,
 when the committed counter summary matches the current sources, the HBM
@@ -107,12 +108,11 @@ def oracle_lines(og, cfg, types, neg_tries, threads):
     return res
 
 
-def kernel_share(total, cand_lines, heavy_lines, kind):
-    """A shape's algorithmic bytes that one of its kernels is charged: in
-    proportion to the lines that the candidate kernel and the kernel that
-    intersects long lists count themselves."""
-    both = cand_lines + heavy_lines
-    return total * (cand_lines if kind == "cand" else heavy_lines) // both if both else 0
+def kernel_share(total, cand, heavy, kind):
+    """A shape's algorithmic bytes that one of its kernels is charged, in
+    proportion to what the candidate kernel and the kernel that intersects
+    long lists read."""
+    return total * (cand if kind == "cand" else heavy) // (cand + heavy) if cand + heavy else 0
 
 
 def workload_name(cfg, types):
@@ -949,12 +949,16 @@ def main():
         if ms is None:
             ms = d["candidate_kernel_ms"] if kind == "cand" else d["long_list_kernel_ms"]
         # the events around 3p's long-list work span its batched kernel and its unit kernel
-        name = (f"k_candidates<{qt}> r0" if kind == "cand" else
-                "k_heavy<3p> r0 + k_units<3p> r0" if qt == "3p" else f"k_finish<{qt}> r0")
+        names = {"cand": f"k_candidates<{qt}> r0",
+                 "heavy": "k_heavy<3p> r0 + k_units<3p> r0" if qt == "3p" else f"k_finish<{qt}> r0"}
+        name = names[kind]
         tally = acct[qt]["cand_lines" if kind == "cand" else "heavy_lines"] * 64
         algo = None
         if lines:
-            algo = kernel_share(lines[qt]["total_bytes"], acct[qt]["cand_lines"], acct[qt]["heavy_lines"], kind)
+            reads = [traffic_for(cfg.name, names[k]) for k in ("cand", "heavy")]
+            if acct[qt]["heavy_lines"] == 0 or None in reads:   # no long list, or no summary
+                reads = [acct[qt]["cand_lines"], acct[qt]["heavy_lines"]]
+            algo = kernel_share(lines[qt]["total_bytes"], *reads, kind)
         traffic = traffic_for(cfg.name, name)
         gbps = lambda nbytes: nbytes / (ms / 1e3) / 1e9 if nbytes is not None and ms > 0 else None
         achieved = gbps(algo)
@@ -984,7 +988,8 @@ def main():
         "lines per query that the oracle's bidirectional check under the strict node cut reads for "
         "the first round's candidate draws (node entries, group search, lists of the device layout), "
         "summed over the batch, and divided between the shape's candidate kernel and the kernel "
-        "that intersects the lists it leaves in the proportion of their own line tallies; "
+        "that intersects the lists it leaves in the proportion of their traffic (their own line "
+        "tallies where no summary matches the sources); "
         "kernel_tally is the kernel's own count of the lines of each read it makes; traffic is "
         "rocprofv3 FETCH_SIZE + WRITE_SIZE scaled by a plain copy")
 
