@@ -2442,13 +2442,14 @@ inline void prof_mark(int which, bool after, hipStream_t st)
 // candidates are answers: one wavefront for the draws 32.1 ms for 3p and 3.7
 // for 2p, sixteen, and a query's draws dealt over several workgroups, 0.30 and
 // 0.20).  3p leaves it no lists of the first draws: calls that fill the GPU
-// run one (Freebase-shaped step 598 us, with four 612).
+// run two (Freebase-shaped 3p 387 us with one or two, with four 395; 6,000 x
+// 300 on an FB15k-237-shaped graph 575 with one, 397 with two).
 template <int QT>
 inline int finish_waves(const SampleParams& p)
 {
     if (p.batch <= FINISH_WAVES / 16) return 16;
     if (p.batch <= FINISH_WAVES / 8) return 8;
-    return QT == Q3P && p.batch >= FINISH_WAVES ? 1 : 4;
+    return QT == Q3P && p.batch >= FINISH_WAVES ? 2 : 4;
 }
 
 // The long-list kernels over the queue (mask: see put_verdict).

@@ -106,3 +106,11 @@ def test_shared_queries_beside_a_call_that_fills_the_gpu(qt):
     for k, out in enumerate(outs):
         ref = og.sample(qt, 16, 500, seed=9, query_offset=16 * k, neg_tries=2000)
         assert_same(to_numpy(out), ref, what=f"{qt} call {k}")
+
+
+# 3p calls that fill the GPU have fewer wavefronts per query
+def test_further_draws_of_a_full_3p_batch():
+    rng = np.random.default_rng(44)
+    g, og = graph_pair(kgsynth.random_tiny(rng, 500, 3, 20000), 500, 3)
+    got = gpu_sample(g, "3p", 4097, 100, seed=5, neg_tries=500)
+    assert_same(got, og.sample("3p", 4097, 100, seed=5, neg_tries=500), what="3p batch 4097")
